@@ -266,9 +266,55 @@ bool vec_ok(const T* p, int64_t ld) {
   return ld % (int64_t)(16 / sizeof(T)) == 0 && (reinterpret_cast<uintptr_t>(p) & 15) == 0;
 }
 
+// The fp64 tile, and the rule by which batches and k ranges are cut in both
+// precisions: 128 x 128 where it gives a workgroup to every CU.
 int pick_tile(int64_t M, int64_t N, int64_t splits) {
   const int64_t big = ((M + 127) / 128) * ((N + 127) / 128) * splits;
   return big >= 256 ? nf::TILE_128x128 : nf::TILE_64x64;
+}
+
+// Microseconds that the wide kernels (fp32) take for `tiles` tiles of `stages`
+// stages of 16 k each, from measurements of the three tiles: a stage costs
+// `alone` however few tiles there are, `share` per tile and CU once the chip
+// is full; a tile's end (epilogue, first operands) costs `end`.
+//   tile        alone  share  end   measured (us, random operands)
+//   64 x 64     0.33   0.21   1.5   16x4096x4096 84; 8192x4096x4096 1740
+//   128 x 128   0.50   0.61   4.5   16x4096x4096 127; 4096x1024x1024 48.5;
+//                                   8192x4096x4096 1243
+//   256 x 256   1.48   2.18   20    16x4096x4096 379; 8192x4096x4096 1116
+// So the 64 x 64 tile wins while the grid is small (3008x520x1024: 33 against
+// 39 and 106), the 128 x 128 tile from about one per CU (4096x1024x1024: 48.5
+// against 63 and 107), the 256 x 256 tile where its own grid fills the chip.
+double wide_cost(int tile, int64_t M, int64_t N, int64_t splits, int64_t stages, int ncu) {
+  struct Cost {
+    int side;
+    double alone, share, end;
+  };
+  static const Cost costs[3] = {{128, 0.50, 0.61, 4.5}, {64, 0.33, 0.212, 1.5}, {256, 1.48, 2.18, 20.0}};
+  const Cost& c = costs[tile];
+  const int64_t tiles = ((M + c.side - 1) / c.side) * ((N + c.side - 1) / c.side) * splits;
+  const int64_t rounds = (tiles + ncu - 1) / ncu;
+  return (double)stages * std::max(c.alone, c.share * (double)rounds) + c.end * (double)rounds;
+}
+
+int device_cus(const nf_net* n) { return n->ncu > 0 ? n->ncu : 256; }
+
+// The tile of a wide contraction in `splits` pieces of `len` k each; `big`:
+// the 256 x 256 tile takes this epilogue.
+int pick_wide_tile(const nf_net* n, int64_t M, int64_t N, int64_t splits, int64_t len, bool big) {
+  const int ncu = device_cus(n);
+  const int64_t stages = (len + 15) / 16;
+  int best = nf::TILE_64x64;
+  double cost = wide_cost(best, M, N, splits, stages, ncu);
+  for (int tile : {(int)nf::TILE_128x128, (int)nf::TILE_256x256}) {
+    if (tile == nf::TILE_256x256 && !big) continue;
+    const double c = wide_cost(tile, M, N, splits, stages, ncu);
+    if (c < cost) {
+      cost = c;
+      best = tile;
+    }
+  }
+  return best;
 }
 
 void clear_recs(nf_net* n) {
@@ -339,30 +385,64 @@ double gemm_bytes(int epi, int M_, int N_, int K_, int nsplit, double esz) {
   }
 }
 
-// tile_override: a TileShape, or -1 to pick one from the grid size
+// One contraction in nsplit pieces of the k range, on the wide kernels in fp32
+// and the general ones in fp64.  small: fp64 takes the 64 x 64 tile.
 template <class T>
 nf_status launch(nf_net* n, int epi, bool akc, bool bkc, bool av, bool bv, int nsplit,
-                 const nf::GemmParamsT<T>& p, hipStream_t s, int tile_override = -1) {
-  const int tile = tile_override >= 0 ? tile_override : pick_tile(p.M, p.N, nsplit);
-  return timed(n, nf::gemm_name(epi, tile, dtype_of<T>()),
-               gemm_bytes(epi, p.M, p.N, p.K, nsplit, (double)sizeof(T)),
-               2.0 * p.M * (double)p.N * p.K, s,
-               [&] { return nf::launch_gemm<T>(epi, tile, akc, bkc, av, bv, nsplit, p, s); });
+                 const nf::GemmParamsT<T>& p, hipStream_t s, bool small = false) {
+  const double bytes = gemm_bytes(epi, p.M, p.N, p.K, nsplit, (double)sizeof(T));
+  const double flops = 2.0 * p.M * (double)p.N * p.K;
+  if constexpr (sizeof(T) == 4) {
+    const bool big = epi == nf::EPI_BWD || epi == nf::EPI_DW_SGD ||
+                     (av && (epi == nf::EPI_FWD_STASH || epi == nf::EPI_FWD_OUT));
+    const int tile = pick_wide_tile(n, p.M, p.N, nsplit, nsplit > 1 ? p.sub_len : p.K, big);
+    nf::GemmGroupT<float> g{};
+    g.p[0] = p;
+    g.n = 1;
+    return timed(n, nf::gemm_name(epi, tile, nf::DT_F32), bytes, flops, s,
+                 [&] { return nf::launch_wide(epi, tile, av, g, &nsplit, s); });
+  } else {
+    const int tile = small ? (int)nf::TILE_64x64 : pick_tile(p.M, p.N, nsplit);
+    return timed(n, nf::gemm_name(epi, tile, nf::DT_F64), bytes, flops, s,
+                 [&] { return nf::launch_gemm<T>(epi, tile, akc, bkc, av, bv, nsplit, p, s); });
+  }
 }
 
 // The cut of a forward contraction (M samples, N units, K inputs) over its
-// k range: one piece unless the 64 x 64 tile grid is under twice the CU count
-// and K >= 256 (general nets take it only when the grid would use the
-// 64 x 64 tile anyway).  Pieces start on whole 16-input stages, so a vector
-// load never reaches into the next piece and every piece start stays 16-byte
-// aligned (nf_split.h).
+// k range.  At most the pieces that bring the 64 x 64 tile grid to twice the
+// CU count, of at least 128 inputs each, 16 at most; none where K < 256 or
+// the grid is that large already (or, for general nets, large enough for the
+// 128 x 128 tile).  fp64 takes that many; in fp32 the count in that range
+// with the least cost is taken, a fold of the pieces (4.5 us and the pieces
+// through memory) included: 3003x517x1001 in one piece takes 32 us, in two
+// 34 and the fold; 16x4096x4096 in one piece 84, in eight 15 and the fold.
+// Pieces start on whole 16-input stages, so a vector load never reaches into
+// the next piece and every piece start stays 16-byte aligned (nf_split.h).
 nf::KSplit fwd_split(const nf_net* n, int64_t M, int64_t N, int64_t K, bool small_tile_only) {
   const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);
-  const int64_t want = 2 * (int64_t)(n->ncu > 0 ? n->ncu : 256);
+  const int64_t want = 2 * (int64_t)device_cus(n);
   if ((small_tile_only && pick_tile(M, N, 1) != nf::TILE_64x64) || tiles >= want || K < 256)
     return nf::KSplit{1, (int)K};
-  const int64_t nsplit = std::min<int64_t>({(want + tiles - 1) / tiles, K / 128, 16});
-  return nf::k_split(K, nsplit);
+  const int64_t most = std::min<int64_t>({(want + tiles - 1) / tiles, K / 128, 16});
+  if (n->dtype == nf::DT_F64) return nf::k_split(K, most);
+  nf::KSplit best{1, (int)K};
+  double cost = 0.0;
+  for (int64_t want_pieces = 1; want_pieces <= most; ++want_pieces) {
+    const nf::KSplit ks = nf::k_split(K, want_pieces);
+    double c = 1e30;
+    for (int tile : {(int)nf::TILE_64x64, (int)nf::TILE_128x128})
+      c = std::min(c, wide_cost(tile, M, N, ks.nsplit, (ks.sub_len + 15) / 16, device_cus(n)));
+    // written and read again at about 4 TB/s; a medium net's per-sample
+    // kernel reads the pieces in any case, without a fold of its own
+    const double through = 2.0 * 4.0 * (double)M * (double)N * ks.nsplit / 4e6;
+    if (ks.nsplit > 1 || !small_tile_only) c += through;
+    if (ks.nsplit > 1 && small_tile_only) c += 4.5;
+    if (want_pieces == 1 || c < cost) {
+      cost = c;
+      best = ks;
+    }
+  }
+  return best;
 }
 
 // The k pieces of the skinny forward kernel (layers of at most
@@ -526,7 +606,7 @@ nf_status run_forward(nf_net* n, const T* x, const T* y, int64_t batch, T* out, 
       q.partial = as<T>(n->partial);
       q.pstride = pstride;
       q.ld0 = ldp;
-      st = launch<T>(n, nf::EPI_FWD_PIECE, true, true, av, true, nsplit, q, s, nf::TILE_64x64);
+      st = launch<T>(n, nf::EPI_FWD_PIECE, true, true, av, true, nsplit, q, s, true);
       if (st != NF_OK) return st;
       nf::FwdFoldParamsT<T> f{};
       f.partial = q.partial;
@@ -687,8 +767,14 @@ nf_status run_backward_update(nf_net* n, const T* x, int64_t batch, double eta, 
   for (size_t i = 0; i < pieces.size(); ++i) {
     if (done[i]) continue;
     const Piece& pi = pieces[i];
-    const LayerLayout& li = n->layers[pi.l];
-    const int tile = pick_tile(li.out, li.in, (int64_t)shards * pi.nsub);
+    auto tile_of = [&](const Piece& pc) {
+      const LayerLayout& ly = n->layers[pc.l];
+      if (sizeof(T) == 4)
+        return pick_wide_tile(n, ly.out, ly.in, (int64_t)shards * pc.nsub,
+                              (shard_len + pc.nsub - 1) / pc.nsub, true);
+      return pick_tile(ly.out, ly.in, (int64_t)shards * pc.nsub);
+    };
+    const int tile = tile_of(pi);
     const bool bv = pi.l == 1 ? vec_ok(x, n->dims[0]) : true;
     nf::GemmGroupT<T> g{};
     int nsplit[nf::GEMM_GROUP_MAX];
@@ -696,10 +782,10 @@ nf_status run_backward_update(nf_net* n, const T* x, int64_t batch, double eta, 
     for (size_t j = i; j < pieces.size() && g.n < nf::GEMM_GROUP_MAX; ++j) {
       if (done[j]) continue;
       const Piece& pj = pieces[j];
-      const LayerLayout& lj = n->layers[pj.l];
-      const int tj = pick_tile(lj.out, lj.in, (int64_t)shards * pj.nsub);
+      const int tj = tile_of(pj);
       const bool bvj = pj.l == 1 ? vec_ok(x, n->dims[0]) : true;
-      if (tj != tile || bvj != bv) continue;
+      // (the wide kernels read B's rows one value at a time, aligned or not)
+      if (tj != tile || (sizeof(T) == 8 && bvj != bv)) continue;
       nf::GemmParamsT<T> p = piece_params(pj);
       nsplit[g.n] = shards * pj.nsub;
       g.p[g.n++] = p;
@@ -708,7 +794,10 @@ nf_status run_backward_update(nf_net* n, const T* x, int64_t batch, double eta, 
       done[j] = true;
     }
     nf_status st = timed(n, nf::gemm_name(nf::EPI_DW_PARTIAL, tile, dtype), bytes, flops, s, [&] {
-      return nf::launch_dw_partial_group<T>(tile, bv, g, nsplit, s);
+      if constexpr (sizeof(T) == 4)
+        return nf::launch_wide(nf::EPI_DW_PARTIAL, tile, true, g, nsplit, s);
+      else
+        return nf::launch_dw_partial_group<T>(tile, bv, g, nsplit, s);
     });
     if (st != NF_OK) return st;
   }
@@ -969,7 +1058,7 @@ nf_status medium_forward_deltas(nf_net* n, const T* x, const T* y, int64_t batch
   }
   if (!skinny) {
     const bool av = vec_ok(x, n->dims[0]);
-    st = launch<T>(n, nf::EPI_FWD_PIECE, true, true, av, true, nsplit, p, s, nf::TILE_64x64);
+    st = launch<T>(n, nf::EPI_FWD_PIECE, true, true, av, true, nsplit, p, s, true);
     if (st != NF_OK) return st;
   }
 

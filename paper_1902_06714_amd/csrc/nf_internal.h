@@ -85,16 +85,24 @@ struct GemmParamsT {
 };
 using GemmParams = GemmParamsT<float>;
 
-// Tile shapes available to the host side.
-enum TileShape : int { TILE_128x128 = 0, TILE_64x64 = 1 };
+// Tile shapes available to the host side (256 x 256 in fp32 only).
+enum TileShape : int { TILE_128x128 = 0, TILE_64x64 = 1, TILE_256x256 = 2 };
 
-// Row pitches and base addresses that allow 16-byte vector loads must be
-// multiples of 16 / sizeof(T) elements and 16-byte aligned.
+// Length in bytes of the buffer resources the contractions read their tiles
+// through: an offset at or past it reads as zero.
+constexpr unsigned TILE_OOB = 0x7ffffff0u;
+
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return fma(a, b, c); }
+
+// The fp64 contraction.  Row pitches and base addresses that allow 16-byte
+// vector loads must be multiples of 16 / sizeof(T) elements and 16-byte
+// aligned.
 template <class T>
 hipError_t launch_gemm(int epi, int tile, bool a_kcontig, bool b_kcontig, bool a_vec, bool b_vec,
                        int nsplit, const GemmParamsT<T>& p, hipStream_t s);
 
-// Name of the kernel instance launch_gemm picks for these arguments.
+// Name of the kernel instance of an epilogue, tile and element type.
 const char* gemm_name(int epi, int tile, int dtype);
 
 // Forward contractions split over the k range (EPI_FWD_PIECE) finish here:
@@ -117,7 +125,7 @@ struct FwdFoldParamsT {
 template <class T>
 hipError_t launch_fwd_fold(int epi, const FwdFoldParamsT<T>& f, hipStream_t s);
 
-// The tendency pieces of up to GEMM_GROUP_MAX layers in one launch
+// The tendency pieces of up to GEMM_GROUP_MAX fp64 layers in one launch
 // (EPI_DW_PARTIAL; both operands mn-contiguous, A rows vectorisable, B rows as
 // b_vec says), problem q split into nsplit[q] pieces.  The workgroup table is
 // filled by the launcher.
@@ -131,6 +139,16 @@ struct GemmGroupT {
 template <class T>
 hipError_t launch_dw_partial_group(int tile, bool b_vec, const GemmGroupT<T>& g,
                                    const int* nsplit, hipStream_t s);
+
+// The fp32 contractions (csrc/nf_wide.h): the problems of g, all of epilogue
+// epi, problem q in nsplit[q] pieces (one problem unless epi is
+// EPI_DW_PARTIAL).  a_vec: A's rows allow 16-byte loads (forward only; B's
+// always must there, and the tendencies read single values).  The epilogues
+// read and write rows of one pitch: ld1 (EPI_FWD_STASH) and ldaux (EPI_BWD)
+// and ldw (EPI_DW_SGD) must equal ld0.  The 256 x 256 tile takes
+// EPI_FWD_STASH, EPI_FWD_OUT (both with a_vec), EPI_BWD and the tendencies.
+hipError_t launch_wide(int epi, int tile, bool a_vec, const GemmGroupT<float>& g, const int* nsplit,
+                       hipStream_t s);
 
 // The tendency pieces of up to GEMM_GROUP_MAX fp32 layers of at most
 // SKINNY_MAX_UNITS units in one launch, operands loaded straight into the

@@ -1,9 +1,9 @@
-// Kernels for mini-batch MLP training on gfx950 (CDNA4), in fp32 (the
-// paper's default real kind) and fp64 (its real64 kind).
+// Kernels for mini-batch MLP training on gfx950 (CDNA4): the general fp64
+// contraction (the paper's real64 kind; fp32 contractions are in nf_wide.h),
+// and the folds of pieces in both precisions.
 //
 // Every layer step of the method is one tiled contraction on the matrix cores
-// (v_mfma_f32_32x32x2_f32, or v_mfma_f64_16x16x4_f64) with the rest of the
-// step fused into its epilogue:
+// (v_mfma_f64_16x16x4_f64) with the rest of the step fused into its epilogue:
 //   forward     Z = A_{l-1} W_l^T, + b_l, activation and its derivative
 //               (section 3.2, Eq. 2; f' is kept for back-propagation)
 //   output      delta_L = (f(z_L) - y) f'(z_L)   (section 3.3)
@@ -22,7 +22,6 @@
 
 namespace nf {
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 // The matrix-core instruction of each element type, as the contraction uses
@@ -31,21 +30,6 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 // accumulator register v of lane l holds C(row(v, l), col(l)) of the block.
 template <class T>
 struct Mma;
-
-template <>
-struct Mma<float> {
-  static constexpr int BLK = 32, KS = 2, NACC = 16;
-  typedef floatx16 acc_t;
-  __device__ static __forceinline__ acc_t mma(float a, float b, acc_t c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-  }
-  __device__ static __forceinline__ int a_row(int l) { return l & 31; }
-  __device__ static __forceinline__ int k_of(int l) { return l >> 5; }
-  __device__ static __forceinline__ int row(int v, int l) {
-    return 8 * (v >> 2) + 4 * (l >> 5) + (v & 3);
-  }
-  __device__ static __forceinline__ int col(int l) { return l & 31; }
-};
 
 template <>
 struct Mma<double> {
@@ -59,9 +43,6 @@ struct Mma<double> {
   __device__ static __forceinline__ int row(int v, int l) { return 4 * v + (l >> 4); }
   __device__ static __forceinline__ int col(int l) { return l & 15; }
 };
-
-__device__ __forceinline__ float fma_t(float a, float b, float c) { return fmaf(a, b, c); }
-__device__ __forceinline__ double fma_t(double a, double b, double c) { return fma(a, b, c); }
 
 // 16 bytes of elements, the unit of a vector load
 template <class T>
@@ -86,8 +67,6 @@ struct alignas(16) Vec16 {
 // elements outside the matrix or past the piece's k range are read at an
 // offset past the buffer, which returns zeros without a memory access.  So
 // every load is unconditional, stages past the end included.
-constexpr unsigned TILE_OOB = 0x7ffffff0u;   // the buffers' length in bytes
-
 template <class T, int R, int BK, int NT, bool KC, bool VEC>
 struct TileLoader {
   static constexpr int VW = Vec16<T>::N;
@@ -518,25 +497,27 @@ hipError_t launch_gemm(int epi, int tile, bool a_kcontig, bool b_kcontig, bool a
                                                     nsplit, p, s);
 }
 
-template hipError_t launch_gemm<float>(int, int, bool, bool, bool, bool, int,
-                                       const GemmParamsT<float>&, hipStream_t);
 template hipError_t launch_gemm<double>(int, int, bool, bool, bool, bool, int,
                                         const GemmParamsT<double>&, hipStream_t);
 
 const char* gemm_name(int epi, int tile, int dtype) {
-  static const char* names[2][2][7] = {
-      {{"gemm_fwd_stash_128x128", "gemm_fwd_delta_128x128", "gemm_fwd_out_128x128",
-        "gemm_bwd_128x128", "gemm_dw_sgd_128x128", "gemm_dw_partial_128x128",
-        "gemm_fwd_piece_128x128"},
-       {"gemm_fwd_stash_64x64", "gemm_fwd_delta_64x64", "gemm_fwd_out_64x64", "gemm_bwd_64x64",
-        "gemm_dw_sgd_64x64", "gemm_dw_partial_64x64", "gemm_fwd_piece_64x64"}},
+  static const char* names[2][3][7] = {
+      {{"wide_fwd_stash_128x128", "wide_fwd_delta_128x128", "wide_fwd_out_128x128",
+        "wide_bwd_128x128", "wide_dw_sgd_128x128", "wide_dw_partial_128x128",
+        "wide_fwd_piece_128x128"},
+       {"wide_fwd_stash_64x64", "wide_fwd_delta_64x64", "wide_fwd_out_64x64", "wide_bwd_64x64",
+        "wide_dw_sgd_64x64", "wide_dw_partial_64x64", "wide_fwd_piece_64x64"},
+       {"wide_fwd_stash_256x256", "wide_fwd_delta_256x256", "wide_fwd_out_256x256",
+        "wide_bwd_256x256", "wide_dw_sgd_256x256", "wide_dw_partial_256x256",
+        "wide_fwd_piece_256x256"}},
       {{"gemm64_fwd_stash_128x128", "gemm64_fwd_delta_128x128", "gemm64_fwd_out_128x128",
         "gemm64_bwd_128x128", "gemm64_dw_sgd_128x128", "gemm64_dw_partial_128x128",
         "gemm64_fwd_piece_128x128"},
        {"gemm64_fwd_stash_64x64", "gemm64_fwd_delta_64x64", "gemm64_fwd_out_64x64",
         "gemm64_bwd_64x64", "gemm64_dw_sgd_64x64", "gemm64_dw_partial_64x64",
         "gemm64_fwd_piece_64x64"}}};
-  if (epi < 0 || epi > 6 || tile < 0 || tile > 1 || dtype < 0 || dtype > 1) return "gemm";
+  if (epi < 0 || epi > 6 || tile < 0 || tile > (dtype == DT_F32 ? 2 : 1) || dtype < 0 || dtype > 1)
+    return "gemm";
   return names[dtype][tile][epi];
 }
 
@@ -632,8 +613,6 @@ hipError_t launch_dw_partial_group(int tile, bool b_vec, const GemmGroupT<T>& g,
                : launch_group<T, 64, 64, 32, 32, PD_64, false>(g, nsplit, s);
 }
 
-template hipError_t launch_dw_partial_group<float>(int, bool, const GemmGroupT<float>&, const int*,
-                                                   hipStream_t);
 template hipError_t launch_dw_partial_group<double>(int, bool, const GemmGroupT<double>&,
                                                     const int*, hipStream_t);
 

@@ -1,0 +1,807 @@
+// The fp32 contractions of every layer that has no kernel of its own (forward,
+// output and hidden deltas, tendencies; sections 3.2 - 3.5), on the bf16
+// matrix cores.
+//
+// An fp32 value x is the sum of three bf16 values to its last bit: h = bf16(x),
+// m = bf16(x - h), l = bf16(x - h - m), each rounded to nearest, so |m| <= 2^-9
+// |x| and |l| <= 2^-18 |x|.  A product a b is then formed as the six products
+// hh, hm, mh, mm, hl, lh (each exact: 8 x 8 significand bits), accumulated in
+// fp32; what is left out (ml, lm, ll) is below 2^-25 |a b|.
+//
+// Why: the fp32 matrix instruction gives 64 flops a clock and SIMD, the bf16
+// one 1024, so six of them are worth 171, 2.7 times as many.  The sums are
+// no less exact: 6 roundings of the accumulator for 16 k, not 8.  Relative
+// errors against fp64, one 32 x 32 block over k uniform operands, six bf16
+// products against v_mfma_f32_32x32x2_f32: k = 16 3.4e-8 / 7.4e-8, 784 4.5e-7 /
+// 5.0e-7, 4096 9.7e-7 / 1.1e-6 (operands of both signs); 5.3e-7 / 8.4e-7
+// (positive operands, k = 4096).
+//
+// What bounds it: on large problems the power limit (8192 x 4096 x 4096 runs
+// at 1.7 - 1.9 GHz with the matrix cores 70% busy), else the vector
+// instructions of the split, 11 for two values, which a wave does not overlap
+// with its own matrix instructions (a second wave on the SIMD does: per
+// matrix instruction 39 clocks alone, 64 with four vector instructions in the
+// same wave, 43 with them in another).  Hence tiles as large as the grid
+// allows, each operand split once per tile on its way to LDS, and for the
+// 64 x 64 tile loading waves of their own.
+// Measured (random operands, sustained, against the fp32 matrix kernel this
+// replaces): forward 8192 x 4096 x 4096 1116 us, 246 TFLOP/s, against 1968;
+// forward 4096 x 1024 x 1024 48.5 us against 77; tendencies 1024 x 1024 over
+// 4096 in four pieces 48 us against 74; 3003 x 517 x 1001 32 us against 34.
+#pragma once
+
+#include <type_traits>
+
+#include "nf_act.h"
+#include "nf_internal.h"
+#include "nf_split.h"
+
+namespace nf {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+
+constexpr int WIDE_KI = 16;      // k of one 32x32x16 matrix instruction
+
+__device__ __forceinline__ unsigned pack_bf16(float a, float b) {
+  const floatx2 f = {a, b};
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(f, bf16x2));
+}
+
+// The three bf16 parts of two values, packed (a in the low half).
+__device__ __forceinline__ void split3(float a, float b, unsigned& h, unsigned& m, unsigned& l) {
+  h = pack_bf16(a, b);
+  const float a1 = a - __builtin_bit_cast(float, h << 16);
+  const float b1 = b - __builtin_bit_cast(float, h & 0xffff0000u);
+  m = pack_bf16(a1, b1);
+  l = pack_bf16(a1 - __builtin_bit_cast(float, m << 16),
+                b1 - __builtin_bit_cast(float, m & 0xffff0000u));
+}
+
+// bytes of LDS: nb stages, and a flag
+constexpr int wide_lds(int BM, int BN, int BK, int nb) {
+  return nb * 3 * (BK / 8) * ((BM + BN) * 16 + 256) + 16;
+}
+
+// Global -> registers -> LDS of one R x BK operand tile X(r, k) by NT threads,
+// Q quads of 4 values each.  In LDS each of the three parts is [BK / 8][R][8]
+// bf16 (the groups of 8 k 128 bytes apart, in other banks): the 8
+// consecutive k of a row that a lane's operand takes are one 16-byte chunk,
+// and the 32 rows of a half-wave's read are contiguous.
+// KC: quad i holds 4 consecutive k of one row, loaded at once (the hardware
+// takes 16-byte loads at any 4-byte address).  VEC: rows are 16-byte aligned
+// and their pitch padding is zero, so a quad may reach past the last k;
+// otherwise the last, partial stage is read one value at a time, since the
+// row's end may be the end of the allocation.  Not KC: a quad holds 4
+// consecutive k of one row from 4 rows of memory, and two quads of a thread
+// that follow one another make a whole chunk.
+template <int R, int BK, int NT, bool KC, bool VEC>
+struct SplitLoader {
+  static constexpr int Q = R * BK / (4 * NT);
+  static constexpr int HALF = R * 16 + 128;      // bytes of 8 k of every row
+  static constexpr int PART = BK / 8 * HALF;     // bytes of one part
+  static_assert(Q >= 1 && Q * 4 * NT == R * BK, "whole quads");
+  static constexpr int C = KC || Q == 1 ? 1 : 2; // quads of a run of k
+  float v[4 * Q];
+
+  // row and k of quad i
+  __device__ __forceinline__ static int row(int tid, int i) {
+    return KC ? (tid + i * NT) / (BK / 4) : (tid + i / C * NT) % R;
+  }
+  __device__ __forceinline__ static int kof(int tid, int i) {
+    return KC ? tid % (BK / 4) * 4 : ((tid + i / C * NT) / R) * 4 * C + i % C * 4;
+  }
+
+  // k0: first k of the stage
+  __device__ __forceinline__ void load(const float* __restrict__ X, int64_t ld, int rmax, int kend,
+                                       int r0, int k0, int tid) {
+    const int left = kend - k0;                  // k of the stage inside the piece
+    const int ldi = (int)ld;
+    if constexpr (KC) {
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+          (void*)(X + (int64_t)r0 * ld + k0), (short)0, (int)TILE_OOB, 0x00020000);
+      const int k = kof(tid, 0);
+      unsigned at[Q];
+#pragma unroll
+      for (int i = 0; i < Q; ++i) {
+        const int r = row(tid, i);
+        at[i] = r0 + r < rmax ? (unsigned)(r * ldi + k) * 4u : TILE_OOB;
+      }
+      if (VEC || left >= BK || left <= 0) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+          const floatx4 u = __builtin_bit_cast(
+              floatx4, __builtin_amdgcn_raw_buffer_load_b128(rs, k < left ? at[i] : TILE_OOB, 0, 0));
+#pragma unroll
+          for (int c = 0; c < 4; ++c) v[4 * i + c] = u[c];
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < Q; ++i)
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            v[4 * i + c] = __builtin_bit_cast(
+                float, __builtin_amdgcn_raw_buffer_load_b32(rs, k + c < left ? at[i] + 4u * c : TILE_OOB, 0, 0));
+      }
+    } else {
+      // the buffer ends at the stage's or the piece's last k
+      const int rows = __builtin_amdgcn_readfirstlane(min(max(left, 0), BK));
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+          (void*)(X + (int64_t)k0 * ld), (short)0, rows * ldi * 4, 0x00020000);
+#pragma unroll
+      for (int i = 0; i < Q; ++i) {
+        const int r = row(tid, i);
+        const unsigned at = r0 + r < rmax ? (unsigned)(r0 + r + kof(tid, i) * ldi) * 4u : TILE_OOB;
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          v[4 * i + c] = __builtin_bit_cast(
+              float, __builtin_amdgcn_raw_buffer_load_b32(rs, at + (unsigned)(c * ldi) * 4u, 0, 0));
+      }
+    }
+  }
+
+  // the values as they are, lds[k][r]
+  __device__ __forceinline__ void store_f32(float* lds, int tid) const {
+#pragma unroll
+    for (int i = 0; i < Q; ++i)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) lds[(kof(tid, i) + c) * R + row(tid, i)] = v[4 * i + c];
+  }
+
+  // each quad's values added to its sum (in the tendencies the sums over the
+  // rows of A are the bias tendencies)
+  __device__ __forceinline__ void add_up(float (&sum)[Q]) const {
+#pragma unroll
+    for (int i = 0; i < Q; ++i)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) sum[i] += v[4 * i + c];
+  }
+
+  // the three parts of every value
+  __device__ __forceinline__ void store(char* lds, int tid) const {
+#pragma unroll
+    for (int i = 0; i < Q; i += C) {
+      unsigned h[2 * C], m[2 * C], l[2 * C];
+#pragma unroll
+      for (int c = 0; c < 2 * C; ++c)
+        split3(v[4 * i + 2 * c], v[4 * i + 2 * c + 1], h[c], m[c], l[c]);
+      const int k = kof(tid, i);
+      char* at = lds + (k >> 3) * HALF + row(tid, i) * 16 + (k & 7) * 2;
+      if constexpr (C == 2) {
+        *reinterpret_cast<uintx4*>(at) = uintx4{h[0], h[1], h[2], h[3]};
+        *reinterpret_cast<uintx4*>(at + PART) = uintx4{m[0], m[1], m[2], m[3]};
+        *reinterpret_cast<uintx4*>(at + 2 * PART) = uintx4{l[0], l[1], l[2], l[3]};
+      } else {
+        *reinterpret_cast<uintx2*>(at) = uintx2{h[0], h[1]};
+        *reinterpret_cast<uintx2*>(at + PART) = uintx2{m[0], m[1]};
+        *reinterpret_cast<uintx2*>(at + 2 * PART) = uintx2{l[0], l[1]};
+      }
+    }
+  }
+};
+
+__device__ __forceinline__ bf16x8 fragment(const char* lds) {
+  return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uintx4*>(lds));
+}
+
+// Buffers over the rows of a tile (BM rows of pitch ld at row m0 of a matrix
+// of M rows): rows past the matrix read as zeros and drop their stores, as do
+// columns whose offset is set past the buffer.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rows(const float* p, int64_t ld, int m0, int M,
+                                                            int BM) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(p + (int64_t)m0 * ld), (short)0,
+                                           min(M - m0, BM) * (int)ld * 4, 0x00020000);
+}
+
+__device__ __forceinline__ void put(const __amdgpu_buffer_rsrc_t& rs, unsigned off, float x) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), rs, off, 0, 0);
+}
+__device__ __forceinline__ float get(const __amdgpu_buffer_rsrc_t& rs, unsigned off) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
+}
+
+// Calls f(i, j, off) for the blocks of the wave's accumulators; entry v of a
+// block lies at off(v) bytes in a tile of pitch ld (past every buffer where
+// the column is past the matrix): accumulator register v of a lane holds row
+// 8 (v / 4) + 4 (lane / 32) + v % 4 and column lane % 32 of its block.
+__device__ __forceinline__ auto block_offsets(int i, int j, int64_t ld, int n0, int N, int wm, int wn,
+                                              int lane) {
+  const int n = n0 + wn + j * 32 + (lane & 31), ldi = (int)ld;
+  const unsigned col = n < N ? (unsigned)((wm + 4 * (lane >> 5)) * ldi + n) * 4u : TILE_OOB;
+  return [=](int v) { return col + (unsigned)((i * 32 + 8 * (v >> 2) + (v & 3)) * ldi) * 4u; };
+}
+template <int TM, int TN, class F>
+__device__ __forceinline__ void each_block(int64_t ld, int n0, int N, int wm, int wn, int lane, F f) {
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      f(i, j, block_offsets(i, j, ld, n0, N, wm, wn, lane));
+      __builtin_amdgcn_sched_barrier(0);   // one block's offsets in registers at a time
+    }
+}
+// The same with the values of a second matrix at those places, read from
+// buffer r: all loads of some blocks before f's stores for them (a load may
+// not move up across the stores, so one at a time each would be waited for).
+template <int TM, int TN, class F>
+__device__ __forceinline__ void with_input(const __amdgpu_buffer_rsrc_t& r, int64_t ld, int n0, int N,
+                                           int wm, int wn, int lane, F f) {
+  constexpr int NB = TM * TN, G = NB > 4 ? 2 : NB;
+#pragma unroll
+  for (int g = 0; g < NB; g += G) {
+    float x[G][16];
+#pragma unroll
+    for (int b = 0; b < G; ++b) {
+      const auto off = block_offsets((g + b) % TM, (g + b) / TM, ld, n0, N, wm, wn, lane);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) x[b][v] = get(r, off(v));
+    }
+#pragma unroll
+    for (int b = 0; b < G; ++b) {
+      f((g + b) % TM, (g + b) / TM, block_offsets((g + b) % TM, (g + b) / TM, ld, n0, N, wm, wn, lane),
+        x[b]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
+
+
+template <int BM, int TM, int TN, int EPI, int ACT>
+__device__ __forceinline__ void forward_epilogue(const GemmParamsT<float>& p, floatx16 (&acc)[TM][TN],
+                                                 int m0, int n0, int wm, int wn, int lane) {
+  float bias[TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const int n = n0 + wn + j * 32 + (lane & 31);
+    bias[j] = n < p.N ? p.bias[n] : 0.f;
+  }
+  const __amdgpu_buffer_rsrc_t r0 = tile_rows(p.out0, p.ld0, m0, p.M, BM);
+  // out1 has out0's pitch (the host checks)
+  const __amdgpu_buffer_rsrc_t r1 = tile_rows(EPI == EPI_FWD_STASH ? p.out1 : p.out0, p.ld0, m0, p.M, BM);
+  each_block<TM, TN>(p.ld0, n0, p.N, wm, wn, lane, [&](int i, int j, auto off) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      float f, fp;
+      act_eval<float>(ACT, acc[i][j][v] + bias[j], f, fp);
+      put(r0, off(v), f);
+      if constexpr (EPI == EPI_FWD_STASH) put(r1, off(v), fp);
+    }
+  });
+}
+
+// The output delta: the targets' rows have a pitch of their own.
+template <int BM, int TM, int TN, int ACT>
+__device__ __forceinline__ void delta_epilogue(const GemmParamsT<float>& p, floatx16 (&acc)[TM][TN],
+                                               int m0, int n0, int wm, int wn, int lane) {
+  const __amdgpu_buffer_rsrc_t r0 = tile_rows(p.out0, p.ld0, m0, p.M, BM);
+  const __amdgpu_buffer_rsrc_t ry = tile_rows(p.aux, p.ldaux, m0, p.M, BM);
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const int n = n0 + wn + j * 32 + (lane & 31), row = wm + 4 * (lane >> 5);
+    const float bias = n < p.N ? p.bias[n] : 0.f;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      float y[16];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int m = row + i * 32 + 8 * (v >> 2) + (v & 3);
+        y[v] = get(ry, n < p.N ? (unsigned)(m * (int)p.ldaux + n) * 4u : TILE_OOB);
+      }
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int m = row + i * 32 + 8 * (v >> 2) + (v & 3);
+        float f, fp;
+        act_eval<float>(ACT, acc[i][j][v] + bias, f, fp);
+        put(r0, n < p.N ? (unsigned)(m * (int)p.ld0 + n) * 4u : TILE_OOB, (f - y[v]) * fp);
+      }
+    }
+  }
+}
+
+template <int BM, int TM, int TN, int EPI>
+__device__ __forceinline__ void wide_epilogue(const GemmParamsT<float>& p, floatx16 (&acc)[TM][TN],
+                                              int m0, int n0, int wm, int wn, int lane, int bz) {
+  if constexpr (EPI == EPI_FWD_STASH || EPI == EPI_FWD_OUT || EPI == EPI_FWD_DELTA) {
+    // one switch per tile, not one per entry
+    auto emit = [&](auto act) {
+      if constexpr (EPI == EPI_FWD_DELTA)
+        delta_epilogue<BM, TM, TN, act.value>(p, acc, m0, n0, wm, wn, lane);
+      else
+        forward_epilogue<BM, TM, TN, EPI, act.value>(p, acc, m0, n0, wm, wn, lane);
+    };
+    switch (p.act) {
+      case ACT_GAUSSIAN: emit(std::integral_constant<int, ACT_GAUSSIAN>()); break;
+      case ACT_RELU: emit(std::integral_constant<int, ACT_RELU>()); break;
+      case ACT_SIGMOID: emit(std::integral_constant<int, ACT_SIGMOID>()); break;
+      case ACT_TANH: emit(std::integral_constant<int, ACT_TANH>()); break;
+      default: emit(std::integral_constant<int, ACT_STEP>()); break;
+    }
+  } else if constexpr (EPI == EPI_BWD) {
+    // aux has out0's pitch; a block's loads before its stores, which the
+    // compiler may not move them across
+    const __amdgpu_buffer_rsrc_t r0 = tile_rows(p.out0, p.ld0, m0, p.M, BM);
+    const __amdgpu_buffer_rsrc_t ra = tile_rows(p.aux, p.ld0, m0, p.M, BM);
+    with_input<TM, TN>(ra, p.ld0, n0, p.N, wm, wn, lane, [&](int i, int j, auto off, const float* x) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) put(r0, off(v), acc[i][j][v] * x[v]);
+    });
+  } else if constexpr (EPI == EPI_DW_SGD) {
+    // the tendencies and both parameter buffers share one pitch
+    const __amdgpu_buffer_rsrc_t rg = tile_rows(p.out0, p.ld0, m0, p.M, BM);
+    const __amdgpu_buffer_rsrc_t ri = tile_rows(p.Win, p.ld0, m0, p.M, BM);
+    const __amdgpu_buffer_rsrc_t rw = tile_rows(p.W, p.ld0, m0, p.M, BM);
+    with_input<TM, TN>(ri, p.ld0, n0, p.N, wm, wn, lane, [&](int i, int j, auto off, const float* x) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const float c = acc[i][j][v];
+        put(rg, off(v), c);
+        put(rw, off(v), fma_t(-p.scale, c, x[v]));
+      }
+    });
+  } else {
+    const __amdgpu_buffer_rsrc_t r0 = tile_rows(p.partial + (int64_t)bz * p.pstride, p.ld0, m0, p.M, BM);
+    each_block<TM, TN>(p.ld0, n0, p.N, wm, wn, lane, [&](int i, int j, auto off) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) put(r0, off(v), acc[i][j][v]);
+    });
+  }
+}
+
+// The k range of piece bz (the whole range outside the piece epilogues), in
+// scalar registers: it comes from divisions, which run on the vector unit, and
+// a buffer access with anything but scalar registers in its resource loops.
+template <int EPI>
+__device__ __forceinline__ void piece_range(const GemmParamsT<float>& p, int bz, int& kbeg, int& kend) {
+  kbeg = 0;
+  kend = p.K;
+  if constexpr (EPI == EPI_DW_SGD || EPI == EPI_DW_PARTIAL || EPI == EPI_FWD_PIECE) {
+    const int shard = bz / p.nsub, sub = bz % p.nsub;
+    const int sb = shard * p.shard_len;
+    kbeg = sb + sub * p.sub_len;
+    kend = __builtin_amdgcn_readfirstlane(min(kbeg + p.sub_len, sb + p.shard_len));
+    kbeg = __builtin_amdgcn_readfirstlane(kbeg);
+  }
+}
+
+template <int TM, int TN>
+__device__ __forceinline__ void clear(floatx16 (&acc)[TM][TN]) {
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+}
+
+// Whether the sums of the six products cannot be trusted.  An operand that is
+// not finite, or that rounds to infinity in bf16, leaves a NaN or an infinity
+// in every sum it enters; operands so small that their last parts are below
+// the smallest normal number, which the matrix cores read as zeros, leave a
+// tiny sum.  Such a tile is done again on the fp32 matrix cores.
+constexpr float WIDE_TINY = 8.271806e-25f;   // 2^-80
+template <int TM, int TN>
+__device__ __forceinline__ bool doubtful(const floatx16 (&acc)[TM][TN]) {
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const float c = fabsf(acc[i][j][v]);
+        bad |= !(c < __builtin_inff()) || (c > 0.f && c < WIDE_TINY);
+      }
+  return bad;
+}
+
+// The fp32 products of one stage held in LDS as [BK][BM] and [BK][BN]: the
+// 32x32x2 fp32 instruction shares the accumulators' layout.
+template <int BM, int BN, int BK, int TM, int TN>
+__device__ __forceinline__ void multiply_f32(const float* as, const float* bs, floatx16 (&acc)[TM][TN],
+                                             int wm, int wn, int lane) {
+#pragma unroll 1
+  for (int k = lane >> 5; k < BK; k += 2) {
+    float x[TM], y[TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) x[i] = as[k * BM + wm + i * 32 + (lane & 31)];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) y[j] = bs[k * BN + wn + j * 32 + (lane & 31)];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[i], y[j], acc[i][j], 0, 0, 0);
+  }
+}
+
+// The bias tendencies of a tile's rows from the sums of the quads of k that
+// each loading thread kept, added in k order.  Starts with a barrier inside.
+template <class LA, int BM, int BK, int EPI>
+__device__ __forceinline__ void put_bias_sums(const GemmParamsT<float>& p, const float (&bsum)[LA::Q],
+                                              int m0, int bz, int tid, float* sums) {
+#pragma unroll
+  for (int i = 0; i < LA::Q; ++i) sums[(LA::kof(tid, i) >> 2) * BM + LA::row(tid, i)] = bsum[i];
+  __syncthreads();
+  const int m = m0 + tid;
+  if (tid < BM && m < p.M) {
+    float g = sums[tid];
+#pragma unroll
+    for (int k = 1; k < BK / 4; ++k) g += sums[tid + k * BM];
+    if constexpr (EPI == EPI_DW_SGD) {
+      p.gbias[m] = g;
+      p.bvec[m] = fma_t(-p.scale, g, p.bin[m]);
+    } else {
+      p.pbias[(int64_t)bz * p.M + m] = g;
+    }
+  }
+}
+
+// The six products of one pair of operand fragments, the small ones first.
+constexpr int WIDE_PA[6] = {2, 0, 1, 1, 0, 0}, WIDE_PB[6] = {0, 2, 1, 0, 1, 0};
+#define NF_MMA(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0)
+
+// One BM x BN tile by (BM / WM) x (BN / WN) waves of WM x WN that all load and
+// multiply.  FD: the next stage's operands are read from LDS into a second set
+// of registers while this stage's are multiplied (one wave per SIMD has
+// nothing else to hide those reads); otherwise a block row's are read just
+// before its products.
+template <int BM, int BN, int WM, int WN, bool FD, bool AKC, bool BKC, bool AV, bool BV, int EPI>
+__device__ __forceinline__ void wide_tile(const GemmParamsT<float>& p, int bx, int by, int bz,
+                                          char* lds) {
+  constexpr int NT = (BM / WM) * (BN / WN) * 64;
+  constexpr int TM = WM / 32, TN = WN / 32, BK = WIDE_KI;
+  typedef SplitLoader<BM, BK, NT, AKC, AV> LA;
+  typedef SplitLoader<BN, BK, NT, BKC, BV> LB;
+  constexpr int STAGE = 3 * (LA::PART + LB::PART);
+  static_assert(2 * STAGE <= wide_lds(BM, BN, BK, 2), "LDS size");
+  static_assert(BK * (BM + BN) * 4 <= 2 * STAGE, "LDS size");
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = (wave % (BM / WM)) * WM;
+  const int wn = (wave / (BM / WM)) * WN;
+  const int m0 = __builtin_amdgcn_readfirstlane(bx * BM), n0 = __builtin_amdgcn_readfirstlane(by * BN);
+  int kbeg, kend;
+  piece_range<EPI>(p, bz, kbeg, kend);
+  const int ntiles = kend > kbeg ? (kend - kbeg + BK - 1) / BK : 0;
+  constexpr bool DW = EPI == EPI_DW_SGD || EPI == EPI_DW_PARTIAL;
+
+  floatx16 acc[TM][TN];
+  clear(acc);
+  float bsum[LA::Q] = {};
+  LA la[2];
+  LB lb[2];
+  auto request = [&](int set, int t) {
+    la[set].load(p.A, p.lda, p.M, kend, m0, kbeg + t * BK, tid);
+    lb[set].load(p.B, p.ldb, p.N, kend, n0, kbeg + t * BK, tid);
+  };
+  auto deliver = [&](int set, char* buf) {
+    la[set].store(buf, tid);
+    lb[set].store(buf + 3 * LA::PART, tid);
+    if constexpr (DW) la[set].add_up(bsum);
+  };
+  const int fa = (lane >> 5) * LA::HALF + (wm + (lane & 31)) * 16;
+  const int fb = (lane >> 5) * LB::HALF + (wn + (lane & 31)) * 16 + 3 * LA::PART;
+  constexpr int NF = FD ? 2 : 1;
+  bf16x8 a[NF][TM][3], b[NF][TN][3];
+  auto fetch_b = [&](int set, const char* buf) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) b[set][j][q] = fragment(buf + fb + j * 512 + q * LB::PART);
+  };
+  auto fetch_a = [&](int set, int i, const char* buf) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) a[set][i][q] = fragment(buf + fa + i * 512 + q * LA::PART);
+  };
+  // the order of a stage's instructions: matrix instructions with the LDS
+  // accesses and a share of the vector instructions between them
+  constexpr int NM = 6 * TM * TN, NR = 3 * (TM + TN);
+  constexpr int NV = 22 * (LA::Q + LB::Q) + (DW ? 4 * LA::Q : 0) + 16;
+  constexpr int VPM = (NV + NM - 1) / NM;
+  // FD: stage t's operands are in fragment set t & 1, stage t + 1 in LDS
+  // buffer (t + 1) & 1, stages t + 2 and t + 3 in the register sets (stage s
+  // in set s & 1).  Otherwise stage t is in LDS buffer t & 1, stages t + 1
+  // and t + 2 in the register sets.
+  auto stage = [&](int cur, int t) {
+    if constexpr (FD) {
+      char* const next = lds + (cur ^ 1) * STAGE;
+      fetch_b(cur ^ 1, next);
+#pragma unroll
+      for (int i = 0; i < TM; ++i) fetch_a(cur ^ 1, i, next);
+#pragma unroll
+      for (int x = 0; x < 6; ++x)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] = NF_MMA(a[cur][i][WIDE_PA[x]], b[cur][j][WIDE_PB[x]], acc[i][j]);
+      deliver(cur, lds + cur * STAGE);
+      request(cur, t + 4);
+#pragma unroll
+      for (int i = 0; i < NM; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        if (i < NR) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, VPM, 0);
+        if (i >= NR) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+      }
+    } else {
+      char* const now = lds + cur * STAGE;
+      fetch_b(0, now);
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        fetch_a(0, i, now);
+#pragma unroll
+        for (int x = 0; x < 6; ++x)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] = NF_MMA(a[0][i][WIDE_PA[x]], b[0][j][WIDE_PB[x]], acc[i][j]);
+      }
+      deliver(cur ^ 1, lds + (cur ^ 1) * STAGE);
+      request(cur ^ 1, t + 3);
+      __builtin_amdgcn_sched_group_barrier(0x100, 3 * TN + 3, 0);
+#pragma unroll
+      for (int i = 0; i < NM; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        if (i % (6 * TN) < 3) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, VPM, 0);
+        if (i % (6 * TN) >= 6) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+      }
+    }
+    __syncthreads();
+  };
+
+  request(0, 0);
+  request(1, 1);
+  deliver(0, lds);
+  request(0, 2);
+  if constexpr (FD) {
+    deliver(1, lds + STAGE);
+    request(1, 3);
+    __syncthreads();
+    fetch_b(0, lds);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) fetch_a(0, i, lds);
+  }
+  __syncthreads();
+  // (an odd last stage is followed by one of zeros)
+  for (int t = 0; t < ntiles; t += 2) {
+    stage(0, t);
+    stage(1, t + 1);
+  }
+
+  if (__syncthreads_or(doubtful(acc))) {
+    float* const as = reinterpret_cast<float*>(lds);
+    float* const bs = as + BK * BM;
+    clear(acc);
+    for (int t = 0; t < ntiles; ++t) {
+      request(0, t);
+      la[0].store_f32(as, tid);
+      lb[0].store_f32(bs, tid);
+      __syncthreads();
+      multiply_f32<BM, BN, BK>(as, bs, acc, wm, wn, lane);
+      __syncthreads();
+    }
+  }
+  wide_epilogue<BM, TM, TN, EPI>(p, acc, m0, n0, wm, wn, lane, bz);
+  if constexpr (DW) {
+    if (by == 0)
+      put_bias_sums<LA, BM, BK, EPI>(p, bsum, m0, bz, tid, reinterpret_cast<float*>(lds));
+  }
+}
+
+// The same by (BM / WM) x (BN / WN) waves that multiply and NP more that load,
+// for the tiles too small to hide the one behind the other within a wave.
+template <int BM, int BN, int WM, int WN, int NP, bool AKC, bool BKC, bool AV, bool BV, int EPI>
+__device__ __forceinline__ void wide_tile_roles(const GemmParamsT<float>& p, int bx, int by, int bz,
+                                                char* lds) {
+  constexpr int NC = (BM / WM) * (BN / WN);    // waves that multiply
+  constexpr int NT = NP * 64;                  // threads that load
+  constexpr int TM = WM / 32, TN = WN / 32, BK = WIDE_KI, NB = 3;
+  typedef SplitLoader<BM, BK, NT, AKC, AV> LA;
+  typedef SplitLoader<BN, BK, NT, BKC, BV> LB;
+  constexpr int STAGE = 3 * (LA::PART + LB::PART);
+  static_assert(NB * STAGE + 16 == wide_lds(BM, BN, BK, NB), "LDS size");
+  static_assert(BK * (BM + BN) * 4 <= NB * STAGE, "LDS size");
+  volatile int* const again = reinterpret_cast<volatile int*>(lds + NB * STAGE);
+
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int m0 = __builtin_amdgcn_readfirstlane(bx * BM), n0 = __builtin_amdgcn_readfirstlane(by * BN);
+  int kbeg, kend;
+  piece_range<EPI>(p, bz, kbeg, kend);
+  const int ntiles = kend > kbeg ? (kend - kbeg + BK - 1) / BK : 0;
+  constexpr bool DW = EPI == EPI_DW_SGD || EPI == EPI_DW_PARTIAL;
+
+  // Both roles meet at the same barriers: one before the first stage, one
+  // after each stage, one for the check of the sums, two for each stage done
+  // again, one for the bias sums.
+  if (wave >= NC) {
+    const int tid = threadIdx.x - NC * 64;
+    LA la[NB];
+    LB lb[NB];
+    float bsum[LA::Q] = {};
+    auto request = [&](int set, int t) {
+      la[set].load(p.A, p.lda, p.M, kend, m0, kbeg + t * BK, tid);
+      lb[set].load(p.B, p.ldb, p.N, kend, n0, kbeg + t * BK, tid);
+    };
+    auto deliver = [&](int set) {
+      la[set].store(lds + set * STAGE, tid);
+      lb[set].store(lds + set * STAGE + 3 * LA::PART, tid);
+      if constexpr (DW) la[set].add_up(bsum);
+    };
+    // stage s passes through register set and LDS buffer s % NB; while stage
+    // t is multiplied stage t + 2 is delivered
+#pragma unroll
+    for (int d = 0; d < NB; ++d) request(d, d);
+    deliver(0);
+    request(0, NB);
+    deliver(1);
+    request(1, NB + 1);
+    if (tid == 0) *again = 0;
+    __syncthreads();
+    for (int t = 0; t < ntiles; t += NB) {
+#pragma unroll
+      for (int d = 0; d < NB; ++d) {
+        if (t + d >= ntiles) break;
+        const int set = (d + 2) % NB;
+        deliver(set);
+        request(set, t + d + 2 + NB);
+        __syncthreads();
+      }
+    }
+    __syncthreads();
+    if (*again) {
+      float* const as = reinterpret_cast<float*>(lds);
+      for (int t = 0; t < ntiles; ++t) {
+        request(0, t);
+        la[0].store_f32(as, tid);
+        lb[0].store_f32(as + BK * BM, tid);
+        __syncthreads();
+        __syncthreads();
+      }
+    }
+    if constexpr (DW) {
+      if (by == 0)
+        put_bias_sums<LA, BM, BK, EPI>(p, bsum, m0, bz, tid, reinterpret_cast<float*>(lds));
+    }
+    return;
+  }
+
+  const int wm = (wave % (BM / WM)) * WM;
+  const int wn = (wave / (BM / WM)) * WN;
+  // the hh products and the five small ones in accumulators of their own: the
+  // chain of dependent matrix instructions is shorter, and the sum of hh is
+  // rounded once for 16 k
+  floatx16 acc[TM][TN], small[TM][TN];
+  clear(acc);
+  clear(small);
+  const int fa = (lane >> 5) * LA::HALF + (wm + (lane & 31)) * 16;
+  const int fb = (lane >> 5) * LB::HALF + (wn + (lane & 31)) * 16 + 3 * LA::PART;
+  bf16x8 a[2][TM][3], b[2][TN][3];
+  auto fetch = [&](int set, int buf) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) a[set][i][q] = fragment(lds + buf * STAGE + fa + i * 512 + q * LA::PART);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) b[set][j][q] = fragment(lds + buf * STAGE + fb + j * 512 + q * LB::PART);
+    }
+  };
+  __syncthreads();
+  fetch(0, 0);
+  for (int t = 0; t < ntiles; t += 2 * NB) {
+#pragma unroll
+    for (int u = 0; u < 2 * NB; ++u) {
+      if (t + u >= ntiles) break;
+      // the next stage's operands are read while this one's are multiplied
+      fetch((u + 1) & 1, (u + 1) % NB);
+#pragma unroll
+      for (int x = 0; x < 6; ++x)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            floatx16& c = x == 5 ? acc[i][j] : small[i][j];
+            c = NF_MMA(a[u & 1][i][WIDE_PA[x]], b[u & 1][j][WIDE_PB[x]], c);
+          }
+      __syncthreads();
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] += small[i][j];
+  if (__any(doubtful(acc)) && lane == 0) *again = 1;
+  __syncthreads();
+  if (*again) {
+    const float* const as = reinterpret_cast<const float*>(lds);
+    clear(acc);
+    for (int t = 0; t < ntiles; ++t) {
+      __syncthreads();
+      multiply_f32<BM, BN, BK>(as, as + BK * BM, acc, wm, wn, lane);
+      __syncthreads();
+    }
+  }
+  if constexpr (DW) {
+    if (by == 0) __syncthreads();
+  }
+  wide_epilogue<BM, TM, TN, EPI>(p, acc, m0, n0, wm, wn, lane, bz);
+}
+
+// How a tile is worked on: waves that load and multiply, with or without the
+// second set of fragments, or loading waves of their own.
+enum WideForm { WIDE_PLAIN, WIDE_AHEAD, WIDE_ROLES };
+
+// Workgroup b runs on XCD b mod 8.  An XCD takes consecutive tiles (the grid
+// is padded to 8 runs of `per`), in bands of 8 tile rows, so that the tiles
+// it works on at one time share their operands in its L2.
+template <int BM, int BN, int WM, int WN, int FORM, bool AKC, bool BKC, bool AV, bool BV, int EPI>
+__global__ void __launch_bounds__((BM / WM) * (BN / WN) * (FORM == WIDE_ROLES ? 128 : 64))
+wide_kernel(const GemmGroupT<float> g, int total, int per) {
+  __shared__ __attribute__((aligned(16))) char lds[wide_lds(BM, BN, WIDE_KI, FORM == WIDE_ROLES ? 3 : 2)];
+  const int b = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if (b >= total) return;
+  int q = 0;
+  if constexpr (EPI == EPI_DW_PARTIAL) {
+#pragma unroll
+    for (int i = 1; i < GEMM_GROUP_MAX; ++i) q += (i < g.n && b >= g.start[i]);
+  }
+  const GemmParamsT<float>& p = g.p[q];
+  const int r = b - g.start[q];
+  const int mt = (p.M + BM - 1) / BM, nt = (p.N + BN - 1) / BN;
+  const int z = r / (mt * nt), rem = r % (mt * nt);
+  const int band = rem / (8 * nt), inb = rem % (8 * nt);
+  const int bh = min(8, mt - band * 8);
+  const int bx = band * 8 + inb % bh, by = inb / bh, bz = __builtin_amdgcn_readfirstlane(z);
+  if constexpr (FORM == WIDE_ROLES)
+    wide_tile_roles<BM, BN, WM, WN, (BM / WM) * (BN / WN), AKC, BKC, AV, BV, EPI>(p, bx, by, bz, lds);
+  else
+    wide_tile<BM, BN, WM, WN, FORM == WIDE_AHEAD, AKC, BKC, AV, BV, EPI>(p, bx, by, bz, lds);
+}
+
+template <int BM, int BN, int WM, int WN, int FORM, bool AKC, bool BKC, bool AV, bool BV, int EPI>
+static hipError_t launch_one(GemmGroupT<float> g, const int* nsplit, hipStream_t s) {
+  g.start[0] = 0;
+  for (int q = 0; q < g.n; ++q)
+    g.start[q + 1] = g.start[q] + ((g.p[q].M + BM - 1) / BM) * ((g.p[q].N + BN - 1) / BN) * nsplit[q];
+  for (int q = g.n + 1; q <= GEMM_GROUP_MAX; ++q) g.start[q] = g.start[g.n];
+  const int total = g.start[g.n], per = (total + 7) / 8;
+  return launch_k(wide_kernel<BM, BN, WM, WN, FORM, AKC, BKC, AV, BV, EPI>, dim3(8 * per),
+                  (BM / WM) * (BN / WN) * (FORM == WIDE_ROLES ? 128 : 64), 0, s, g, total, per);
+}
+
+template <int BM, int BN, int WM, int WN, int FORM>
+static hipError_t wide_dispatch(int epi, bool av, const GemmGroupT<float>& g, const int* nsplit,
+                                hipStream_t s) {
+#define NF_CASE(E, AKC, BKC, AV) \
+  if (epi == E && av == AV)      \
+    return launch_one<BM, BN, WM, WN, FORM, AKC, BKC, AV, true, E>(g, nsplit, s);
+  // forward: A = activations [m][k], B(k, n) = W[n][k]
+  NF_CASE(EPI_FWD_STASH, true, true, true)
+  NF_CASE(EPI_FWD_OUT, true, true, true)
+  if constexpr (BM < 256) {
+    NF_CASE(EPI_FWD_STASH, true, true, false)
+    NF_CASE(EPI_FWD_DELTA, true, true, true)
+    NF_CASE(EPI_FWD_DELTA, true, true, false)
+    NF_CASE(EPI_FWD_OUT, true, true, false)
+    NF_CASE(EPI_FWD_PIECE, true, true, true)
+    NF_CASE(EPI_FWD_PIECE, true, true, false)
+  }
+  // backward: A = delta [m][k], B(k, n) = W[k][n]
+  NF_CASE(EPI_BWD, true, false, true)
+  // tendencies: A(m, k) = delta[k][m], B(k, n) = activations[k][n], read one
+  // value at a time, so any row pitch will do
+  NF_CASE(EPI_DW_SGD, false, false, true)
+  NF_CASE(EPI_DW_PARTIAL, false, false, true)
+#undef NF_CASE
+  return hipErrorInvalidValue;
+}
+
+}  // namespace nf
