@@ -26,7 +26,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libnf.so")
 SOURCES = ["nf_api.hip", "nf_kernels.hip", "nf_narrow.hip", "nf_narrow64.hip", "nf_medium.hip",
            "nf_eval.hip", "nf_calib.hip", "nf_skinny.hip",
-           "nf_wide256.hip", "nf_wide128.hip", "nf_wide64.hip"]
+           "nf_wide256.hip", "nf_wide128.hip", "nf_wide64.hip",
+           "nf_params.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",

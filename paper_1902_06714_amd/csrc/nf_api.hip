@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
@@ -11,6 +12,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <thread>
 #include <type_traits>
 #include <vector>
 
@@ -113,6 +115,12 @@ struct nf_net {
   void* w1pack = nullptr;
   int64_t w1f_elems = 0;
   uint64_t pver = 1, packver = 0;
+  // pinned host memory that parameters and tendencies pass through: slots of
+  // slot_bytes each; null when it could not be had (they are then copied
+  // matrix by matrix)
+  void* staging = nullptr;
+  int64_t slot_bytes = 0;
+  int slots = 0;
   hipStream_t last = nullptr;
   bool used = false;
   // samples whose f'(z_l), l < L, the last training step left in fbuf (0 when
@@ -157,7 +165,8 @@ nf_status sync_net(nf_net* n) {
   return NF_OK;
 }
 
-// the parameter buffers, the tendencies and the packed copies of W_1
+// the parameter buffers, the tendencies, the packed copies of W_1 and the
+// staging memory
 void free_params(nf_net* n) {
   for (void*& b : n->pbuf) {
     if (b) (void)hipFree(b);
@@ -165,8 +174,10 @@ void free_params(nf_net* n) {
   }
   if (n->grads) (void)hipFree(n->grads);
   if (n->w1pack) (void)hipFree(n->w1pack);
+  if (n->staging) (void)hipHostFree(n->staging);
   n->grads = nullptr;
   n->w1pack = nullptr;
+  n->staging = nullptr;
 }
 
 void free_ws(nf_net* n) {
@@ -1184,6 +1195,15 @@ nf_status guarded(F&& f) {
   }
 }
 
+// Parameters pass through pinned slots of this size, small enough to be in
+// cache when the host copies them and large enough that PCIe, not the launch,
+// sets a slot's time.  Up to kSlots of them, each worked by a thread of its
+// own: one host thread faults in and fills new memory at about 10 GB/s
+// (reading 4096^4-10, 202 MB: one slot 20.6 ms, three 8.8, eight 5.1; 784-
+// 1024^3-10, 11.7 MB: 0.81, 0.36, 0.38).
+constexpr int64_t kSlotBytes = 1 << 20;
+constexpr int kSlots = 8;
+
 nf_status create(const int32_t* dims, int32_t n_dims, const int32_t* acts, int32_t n_acts,
                  int32_t dtype, nf_net** out) {
   if (!out) return fail(NF_EINVAL, "out is NULL");
@@ -1268,8 +1288,96 @@ nf_status create(const int32_t* dims, int32_t n_dims, const int32_t* acts, int32
     return fail(e == hipErrorOutOfMemory ? NF_ENOMEM : NF_EDEVICE,
                 std::string("device allocation failed: ") + hipGetErrorString(e));
   }
+  const int64_t pbytes = round_up(n->n_params * (int64_t)n->esz, 16);
+  n->slot_bytes = std::min(pbytes, kSlotBytes);
+  n->slots = (int)std::min<int64_t>(kSlots, (pbytes + n->slot_bytes - 1) / n->slot_bytes);
+  if (hipHostMalloc(&n->staging, (size_t)(n->slot_bytes * n->slots), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    n->staging = nullptr;
+  }
   *out = n;
   return NF_OK;
+}
+
+// Canonical elements [first, first + count) of slot memory buf to or from dev.
+template <class T>
+hipError_t move_canonical(const nf_net* n, bool to_buf, T* buf, T* dev, int64_t first,
+                          int64_t count) {
+  nf::CanonicalSegs g{};
+  int64_t canon = 0, done = 0;
+  const int L = num_layers(n);
+  // the parts that overlap the range, CANONICAL_SEGS of them per launch
+  for (int l = 1; l <= L && canon < first + count; ++l) {
+    const LayerLayout& ly = n->layers[l];
+    for (int part = 0; part < 2; ++part) {
+      const int64_t elems = part == 0 ? (int64_t)ly.out * ly.in : ly.out;
+      if (canon + elems > first && canon < first + count)
+        g.s[g.n++] = {canon, part == 0 ? ly.w_off : ly.b_off, part == 0 ? ly.ldw : (int64_t)ly.out,
+                      part == 0 ? ly.in : ly.out};
+      canon += elems;
+      const bool last = canon >= first + count;
+      if (g.n == nf::CANONICAL_SEGS || (last && g.n > 0)) {
+        // a launch starts on a whole 16 bytes of the slot: the one before
+        // ends there, short of this part's end by less than that
+        constexpr int64_t VW = 16 / (int64_t)sizeof(T);
+        const int64_t end = last ? count : (canon - first) / VW * VW;
+        if (end > done) {
+          const hipError_t e =
+              nf::launch_canonical<T>(to_buf, g, buf + done, dev, first + done, end - done, nullptr);
+          if (e != hipSuccess) return e;
+          done = end;
+        }
+        if (last) return hipSuccess;
+        // keep the parts that still hold elements of the range
+        int keep = 0;
+        for (int q = 0; q < g.n; ++q) {
+          const int64_t stop = q + 1 < g.n ? g.s[q + 1].start : canon;
+          if (stop > first + done) g.s[keep++] = g.s[q];
+        }
+        g.n = keep;
+      }
+    }
+  }
+  return hipSuccess;
+}
+
+// All canonical elements through the slots, slot t's by thread t.
+template <class T>
+hipError_t stage_params(const nf_net* n, T* dev, const T* host_src, T* host_dst) {
+  const int64_t per = n->slot_bytes / (int64_t)sizeof(T);
+  const int64_t chunks = (n->n_params + per - 1) / per;
+  const int workers = (int)std::min<int64_t>(n->slots, chunks);
+  std::atomic<int> failed{(int)hipSuccess};
+  auto work = [&](int t) {
+    T* buf = reinterpret_cast<T*>(static_cast<char*>(n->staging) + t * n->slot_bytes);
+    hipEvent_t ev = nullptr;
+    hipError_t e = hipSetDevice(n->device);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+    for (int64_t c = t; e == hipSuccess && c < chunks && failed == (int)hipSuccess; c += workers) {
+      const int64_t first = c * per, count = std::min(per, n->n_params - first);
+      if (host_src) std::memcpy(buf, host_src + first, (size_t)count * sizeof(T));
+      e = move_canonical<T>(n, !host_src, buf, dev, first, count);
+      if (e == hipSuccess) e = hipEventRecord(ev, nullptr);
+      if (e == hipSuccess) e = hipEventSynchronize(ev);
+      if (e == hipSuccess && host_dst)
+        std::memcpy(host_dst + first, buf, (size_t)count * sizeof(T));
+    }
+    if (ev) (void)hipEventDestroy(ev);
+    int none = (int)hipSuccess;
+    if (e != hipSuccess) failed.compare_exchange_strong(none, (int)e);
+  };
+  std::vector<std::thread> threads;
+  int started = 1;
+  try {
+    threads.reserve((size_t)workers);
+    for (; started < workers; ++started) threads.emplace_back(work, started);
+  } catch (const std::exception&) {
+    // no more threads to be had: the caller's does the rest
+  }
+  work(0);
+  for (int t = started; t < workers; ++t) work(t);
+  for (std::thread& t : threads) t.join();
+  return (hipError_t)failed.load();
 }
 
 // canonical host array <-> device layout (host_src to dev, or dev to host_dst)
@@ -1281,6 +1389,16 @@ nf_status copy_params(nf_net* n, void* dev, const void* host_src, void* host_dst
   if (st != NF_OK) return st;
   if (host_src) ++n->pver;   // the packed copies of W_1 no longer match
   const size_t es = n->esz;
+  if (n->staging) {
+    const hipError_t e =
+        n->dtype == nf::DT_F64
+            ? stage_params<double>(n, static_cast<double*>(dev), static_cast<const double*>(host_src),
+                                   static_cast<double*>(host_dst))
+            : stage_params<float>(n, static_cast<float*>(dev), static_cast<const float*>(host_src),
+                                  static_cast<float*>(host_dst));
+    if (e != hipSuccess) return hip_fail(e, "parameter copy");
+    return NF_OK;
+  }
   char* d = static_cast<char*>(dev);
   int64_t canon = 0;
   for (size_t l = 1; l < n->layers.size(); ++l) {

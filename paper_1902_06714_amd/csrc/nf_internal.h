@@ -364,6 +364,25 @@ constexpr int MEDIUM64_LDS_WEIGHTS = 15360;
 template <class T>
 hipError_t launch_medium(const MediumParamsT<T>& p, int ncu, hipStream_t s);
 
+// Parts of the canonical order (weights: rows of cols elements at pitch ld;
+// biases: one row), by their first canonical element, and where each lies in
+// the device layout.
+constexpr int CANONICAL_SEGS = 16;
+struct CanonicalSeg {
+  int64_t start, off, ld;
+  int cols;
+};
+struct CanonicalSegs {
+  CanonicalSeg s[CANONICAL_SEGS];
+  int n;
+};
+// Canonical elements [first, first + count), which lie in g's parts, from dev
+// (device layout) to buf or back; buf (16-byte aligned, whole 16 bytes) is
+// memory that the device can address.
+template <class T>
+hipError_t launch_canonical(bool to_buf, const CanonicalSegs& g, T* buf, T* dev, int64_t first,
+                            int64_t count, hipStream_t s);
+
 // Adds to *count the number of rows s < n for which out[s][0..d) and
 // y[s][0..d) have their first largest entry at the same index (rows holding a
 // NaN never count).  Row pitches ldo and ldy in elements.
