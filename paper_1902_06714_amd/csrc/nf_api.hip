@@ -296,30 +296,33 @@ int pick_tile(int64_t M, int64_t N, int64_t splits) {
 // So the 64 x 64 tile wins while the grid is small (3008x520x1024: 33 against
 // 39 and 106), the 128 x 128 tile from about one per CU (4096x1024x1024: 48.5
 // against 63 and 107), the 256 x 256 tile where its own grid fills the chip.
-double wide_cost(int tile, int64_t M, int64_t N, int64_t splits, int64_t stages, int ncu) {
+int64_t wide_tiles(int tile, int64_t M, int64_t N) {
+  const int64_t side = tile == nf::TILE_256x256 ? 256 : (tile == nf::TILE_128x128 ? 128 : 64);
+  return ((M + side - 1) / side) * ((N + side - 1) / side);
+}
+double wide_cost(int tile, int64_t tiles, int64_t stages, int ncu) {
   struct Cost {
-    int side;
     double alone, share, end;
   };
-  static const Cost costs[3] = {{128, 0.50, 0.61, 4.5}, {64, 0.33, 0.212, 1.5}, {256, 1.48, 2.18, 20.0}};
+  static const Cost costs[3] = {{0.50, 0.61, 4.5}, {0.33, 0.212, 1.5}, {1.48, 2.18, 20.0}};
   const Cost& c = costs[tile];
-  const int64_t tiles = ((M + c.side - 1) / c.side) * ((N + c.side - 1) / c.side) * splits;
   const int64_t rounds = (tiles + ncu - 1) / ncu;
   return (double)stages * std::max(c.alone, c.share * (double)rounds) + c.end * (double)rounds;
 }
 
 int device_cus(const nf_net* n) { return n->ncu > 0 ? n->ncu : 256; }
 
-// The tile of a wide contraction in `splits` pieces of `len` k each; `big`:
-// the 256 x 256 tile takes this epilogue.
-int pick_wide_tile(const nf_net* n, int64_t M, int64_t N, int64_t splits, int64_t len, bool big) {
+// The tile of one launch of wide contractions of `len` k each: `tiles` gives
+// the launch's tiles of a shape; `big`: the 256 x 256 tile takes the epilogue.
+template <class F>
+int pick_wide_tile(const nf_net* n, int64_t len, bool big, F&& tiles) {
   const int ncu = device_cus(n);
   const int64_t stages = (len + 15) / 16;
   int best = nf::TILE_64x64;
-  double cost = wide_cost(best, M, N, splits, stages, ncu);
+  double cost = wide_cost(best, tiles(best), stages, ncu);
   for (int tile : {(int)nf::TILE_128x128, (int)nf::TILE_256x256}) {
     if (tile == nf::TILE_256x256 && !big) continue;
-    const double c = wide_cost(tile, M, N, splits, stages, ncu);
+    const double c = wide_cost(tile, tiles(tile), stages, ncu);
     if (c < cost) {
       cost = c;
       best = tile;
@@ -391,7 +394,8 @@ double gemm_bytes(int epi, int M_, int N_, int K_, int nsplit, double esz) {
     case nf::EPI_FWD_OUT: return esz * (M * K + N * K + N + M * N);
     case nf::EPI_BWD: return esz * (M * K + K * N + 2 * M * N);
     case nf::EPI_DW_SGD: return esz * (K * M + K * N + 3 * M * N + 3 * M);
-    case nf::EPI_FWD_PIECE: return esz * (M * K + N * K + nsplit * M * N);
+    case nf::EPI_FWD_PIECE:
+    case nf::EPI_BWD_PIECE: return esz * (M * K + N * K + nsplit * M * N);
     default: return esz * (K * M + K * N + nsplit * (M * N + M));
   }
 }
@@ -406,7 +410,8 @@ nf_status launch(nf_net* n, int epi, bool akc, bool bkc, bool av, bool bv, int n
   if constexpr (sizeof(T) == 4) {
     const bool big = epi == nf::EPI_BWD || epi == nf::EPI_DW_SGD ||
                      (av && (epi == nf::EPI_FWD_STASH || epi == nf::EPI_FWD_OUT));
-    const int tile = pick_wide_tile(n, p.M, p.N, nsplit, nsplit > 1 ? p.sub_len : p.K, big);
+    const int tile = pick_wide_tile(n, nsplit > 1 ? p.sub_len : p.K, big,
+                                    [&](int t) { return wide_tiles(t, p.M, p.N) * nsplit; });
     nf::GemmGroupT<float> g{};
     g.p[0] = p;
     g.n = 1;
@@ -442,7 +447,8 @@ nf::KSplit fwd_split(const nf_net* n, int64_t M, int64_t N, int64_t K, bool smal
     const nf::KSplit ks = nf::k_split(K, want_pieces);
     double c = 1e30;
     for (int tile : {(int)nf::TILE_64x64, (int)nf::TILE_128x128})
-      c = std::min(c, wide_cost(tile, M, N, ks.nsplit, (ks.sub_len + 15) / 16, device_cus(n)));
+      c = std::min(c, wide_cost(tile, wide_tiles(tile, M, N) * ks.nsplit, (ks.sub_len + 15) / 16,
+                                device_cus(n)));
     // written and read again at about 4 TB/s; a medium net's per-sample
     // kernel reads the pieces in any case, without a fold of its own
     const double through = 2.0 * 4.0 * (double)M * (double)N * ks.nsplit / 4e6;
@@ -645,8 +651,11 @@ nf_status run_forward(nf_net* n, const T* x, const T* y, int64_t batch, T* out, 
   return NF_OK;
 }
 
-// Back-propagation and the SGD step (sections 3.3-3.5).  Layer l's weights are
-// updated only after delta_{l-1}, which reads them, has been formed.
+// Back-propagation and the SGD step (sections 3.3-3.5): every delta, then the
+// tendencies and updates, which go to the other parameter buffer.
+template <class T>
+int64_t partial_need(const nf_net* n, const T* x, int64_t batch, int shards);
+
 template <class T>
 nf_status run_backward_update(nf_net* n, const T* x, int64_t batch, double eta, int shards,
                               hipStream_t s, bool deltas_done = false) {
@@ -691,29 +700,80 @@ nf_status run_backward_update(nf_net* n, const T* x, int64_t batch, double eta, 
     return p;
   };
 
-  for (int l = L; l >= 1; --l) {
+  // The deltas.  A contraction with a long k range (the units above) and few
+  // tiles is split over it as the forward ones are, as far as its pieces fit
+  // in the piece buffer that the step has in any case (784-670-2252-259-27 at
+  // 32 samples: 48 us for its widest delta in one piece, 11.5 split).
+  const int64_t room = L > 1 && !deltas_done ? partial_need<T>(n, x, batch, shards) : 0;
+  for (int l = L; l > 1 && !deltas_done; --l) {
     const LayerLayout& ly = n->layers[l];
-    if (l > 1 && !deltas_done) {
-      // delta_{l-1} = (delta_l W_l) * f'(z_{l-1}), with this step's W_l
-      const LayerLayout& lp = n->layers[l - 1];
-      nf::GemmParamsT<T> p{};
-      p.A = as<T>(n->dbuf[l]);
-      p.lda = ly.lda;
-      p.B = P + ly.w_off;
-      p.ldb = ly.ldw;
-      p.M = (int)batch;
-      p.N = lp.out;
-      p.K = ly.out;
-      p.nsub = 1;
-      p.aux = as<T>(n->fbuf[l - 1]);
-      p.ldaux = lp.lda;
-      p.out0 = as<T>(n->dbuf[l - 1]);
-      p.ld0 = lp.lda;
-      nf_status st = launch<T>(n, nf::EPI_BWD, true, false, true, true, 1, p, s);
+    // delta_{l-1} = (delta_l W_l) * f'(z_{l-1}), with this step's W_l
+    const LayerLayout& lp = n->layers[l - 1];
+    nf::GemmParamsT<T> p{};
+    p.A = as<T>(n->dbuf[l]);
+    p.lda = ly.lda;
+    p.B = P + ly.w_off;
+    p.ldb = ly.ldw;
+    p.M = (int)batch;
+    p.N = lp.out;
+    p.K = ly.out;
+    p.nsub = 1;
+    p.aux = as<T>(n->fbuf[l - 1]);
+    p.ldaux = lp.lda;
+    p.out0 = as<T>(n->dbuf[l - 1]);
+    p.ld0 = lp.lda;
+    const int64_t ldp = round_up(p.N, 4);
+    const int64_t pstride = round_up((int64_t)p.M * ldp, kAlign);
+    nf::KSplit ks = fwd_split(n, p.M, p.N, p.K, true);
+    if (ks.nsplit > 1 && ks.nsplit * pstride > room) ks = nf::k_split(p.K, room / pstride);
+    nf_status st;
+    if (ks.nsplit <= 1) {
+      st = launch<T>(n, nf::EPI_BWD, true, false, true, true, 1, p, s);
+    } else {
+      st = ensure_partial(n, room);
       if (st != NF_OK) return st;
+      nf::GemmParamsT<T> q = p;
+      q.shard_len = p.K;
+      q.nsub = ks.nsplit;
+      q.sub_len = ks.sub_len;
+      q.partial = as<T>(n->partial);
+      q.pstride = pstride;
+      q.ld0 = ldp;
+      st = launch<T>(n, nf::EPI_BWD_PIECE, true, false, true, true, ks.nsplit, q, s, true);
+      if (st != NF_OK) return st;
+      nf::FwdFoldParamsT<T> f{};
+      f.partial = q.partial;
+      f.pstride = pstride;
+      f.ldp = ldp;
+      f.nsplit = ks.nsplit;
+      f.M = p.M;
+      f.N = p.N;
+      f.out0 = p.out0;
+      f.ld0 = p.ld0;
+      f.aux = p.aux;
+      f.ldaux = p.ldaux;
+      const double mn = (double)p.M * p.N;
+      st = timed(n, sizeof(T) == 8 ? "bwd64_fold" : "bwd_fold",
+                 (double)sizeof(T) * mn * (ks.nsplit + 2), mn * ks.nsplit, s,
+                 [&] { return nf::launch_fwd_fold<T>(nf::EPI_BWD, f, s); });
     }
-    if (!piece_of(l)) {
-      const bool bv = l == 1 ? vec_ok(x, n->dims[0]) : true;
+    if (st != NF_OK) return st;
+  }
+
+  // the layers whose batch is one piece, several to a launch (their small
+  // grids then run side by side: 784-73-40-88-10 at 211 samples 33.7 us in four
+  // launches, 9.5 in one)
+  for (int l = L; l >= 1;) {
+    nf::GemmGroupT<T> g{};
+    double bytes = 0.0, flops = 0.0;
+    bool bv = true;
+    for (; l >= 1 && g.n < nf::GEMM_GROUP_MAX; --l) {
+      if (piece_of(l)) continue;
+      const LayerLayout& ly = n->layers[l];
+      // fp64 reads B's rows with vectors where all of a launch's allow it
+      const bool bvl = sizeof(T) == 4 || l > 1 || vec_ok(x, n->dims[0]);
+      if (g.n > 0 && bvl != bv) break;
+      bv = bvl;
       nf::GemmParamsT<T> p = dw_params(l);
       p.nsub = 1;
       p.sub_len = (int)shard_len;
@@ -725,9 +785,29 @@ nf_status run_backward_update(nf_net* n, const T* x, int64_t batch, double eta, 
       p.bvec = Q + ly.b_off;
       p.bin = P + ly.b_off;
       p.gbias = G + ly.b_off;
-      nf_status st = launch<T>(n, nf::EPI_DW_SGD, false, false, true, bv, 1, p, s);
-      if (st != NF_OK) return st;
+      g.p[g.n++] = p;
+      bytes += gemm_bytes(nf::EPI_DW_SGD, p.M, p.N, p.K, 1, (double)sizeof(T));
+      flops += 2.0 * p.M * (double)p.N * p.K;
     }
+    if (g.n == 0) continue;
+    auto tiles_of = [&](int t) {
+      int64_t tiles = 0;
+      for (int q = 0; q < g.n; ++q) tiles += wide_tiles(t, g.p[q].M, g.p[q].N);
+      return tiles;
+    };
+    static const int one[nf::GEMM_GROUP_MAX] = {1, 1, 1, 1};
+    nf_status st;
+    if constexpr (sizeof(T) == 4) {
+      const int tile = pick_wide_tile(n, batch, true, tiles_of);
+      st = timed(n, nf::gemm_name(nf::EPI_DW_SGD, tile, nf::DT_F32), bytes, flops, s,
+                 [&] { return nf::launch_wide(nf::EPI_DW_SGD, tile, true, g, one, s); });
+    } else {
+      const int tile = tiles_of(nf::TILE_128x128) >= 256 ? nf::TILE_128x128 : nf::TILE_64x64;
+      st = timed(n, nf::gemm_name(nf::EPI_DW_SGD, tile, nf::DT_F64), bytes, flops, s, [&] {
+        return nf::launch_dw_group<T>(nf::EPI_DW_SGD, tile, bv, g, one, s);
+      });
+    }
+    if (st != NF_OK) return st;
   }
   if (pieces.empty()) return NF_OK;
 
@@ -781,8 +861,9 @@ nf_status run_backward_update(nf_net* n, const T* x, int64_t batch, double eta, 
     auto tile_of = [&](const Piece& pc) {
       const LayerLayout& ly = n->layers[pc.l];
       if (sizeof(T) == 4)
-        return pick_wide_tile(n, ly.out, ly.in, (int64_t)shards * pc.nsub,
-                              (shard_len + pc.nsub - 1) / pc.nsub, true);
+        return pick_wide_tile(n, (shard_len + pc.nsub - 1) / pc.nsub, true, [&](int t) {
+          return wide_tiles(t, ly.out, ly.in) * shards * pc.nsub;
+        });
       return pick_tile(ly.out, ly.in, (int64_t)shards * pc.nsub);
     };
     const int tile = tile_of(pi);
@@ -808,7 +889,7 @@ nf_status run_backward_update(nf_net* n, const T* x, int64_t batch, double eta, 
       if constexpr (sizeof(T) == 4)
         return nf::launch_wide(nf::EPI_DW_PARTIAL, tile, true, g, nsplit, s);
       else
-        return nf::launch_dw_partial_group<T>(tile, bv, g, nsplit, s);
+        return nf::launch_dw_group<T>(nf::EPI_DW_PARTIAL, tile, bv, g, nsplit, s);
     });
     if (st != NF_OK) return st;
   }

@@ -44,7 +44,8 @@ enum Epilogue : int {
   EPI_BWD = 3,        // out0 = C * aux                          (hidden delta)
   EPI_DW_SGD = 4,     // G = C; W -= scale * C; bias sums and update
   EPI_DW_PARTIAL = 5, // partial[split] = C; bias partial sums
-  EPI_FWD_PIECE = 6   // forward operands, partial[piece] = C over a piece of the k range
+  EPI_FWD_PIECE = 6,  // forward operands, partial[piece] = C over a piece of the k range
+  EPI_BWD_PIECE = 7   // the same with the backward operands
 };
 
 // Element types of a network's parameters and per-sample buffers.
@@ -105,9 +106,10 @@ hipError_t launch_gemm(int epi, int tile, bool a_kcontig, bool b_kcontig, bool a
 // Name of the kernel instance of an epilogue, tile and element type.
 const char* gemm_name(int epi, int tile, int dtype);
 
-// Forward contractions split over the k range (EPI_FWD_PIECE) finish here:
+// Contractions split over the k range finish here.  Forward (EPI_FWD_PIECE):
 // z = sum of the pieces in piece order + b[n], then the forward epilogue
-// `epi` (EPI_FWD_STASH, EPI_FWD_DELTA or EPI_FWD_OUT) on z.
+// `epi` (EPI_FWD_STASH, EPI_FWD_DELTA or EPI_FWD_OUT) on z.  Backward
+// (EPI_BWD_PIECE): `epi` EPI_BWD, out0 = the sum times aux.
 template <class T>
 struct FwdFoldParamsT {
   const T* partial;                        // [nsplit][M][ldp]
@@ -119,16 +121,16 @@ struct FwdFoldParamsT {
   int64_t ld0;
   T* out1;                                 // EPI_FWD_STASH: f'(z) [M][ld1]
   int64_t ld1;
-  const T* aux;                            // EPI_FWD_DELTA: y [M][ldaux]
+  const T* aux;                            // EPI_FWD_DELTA: y, EPI_BWD: f'(z) [M][ldaux]
   int64_t ldaux;
 };
 template <class T>
 hipError_t launch_fwd_fold(int epi, const FwdFoldParamsT<T>& f, hipStream_t s);
 
-// The tendency pieces of up to GEMM_GROUP_MAX fp64 layers in one launch
-// (EPI_DW_PARTIAL; both operands mn-contiguous, A rows vectorisable, B rows as
-// b_vec says), problem q split into nsplit[q] pieces.  The workgroup table is
-// filled by the launcher.
+// The tendencies of up to GEMM_GROUP_MAX fp64 layers in one launch
+// (EPI_DW_PARTIAL, or EPI_DW_SGD with one piece each; both operands
+// mn-contiguous, A rows vectorisable, B rows as b_vec says), problem q split
+// into nsplit[q] pieces.  The workgroup table is filled by the launcher.
 constexpr int GEMM_GROUP_MAX = 4;
 template <class T>
 struct GemmGroupT {
@@ -137,12 +139,12 @@ struct GemmGroupT {
   int n;                                   // problems
 };
 template <class T>
-hipError_t launch_dw_partial_group(int tile, bool b_vec, const GemmGroupT<T>& g,
-                                   const int* nsplit, hipStream_t s);
+hipError_t launch_dw_group(int epi, int tile, bool b_vec, const GemmGroupT<T>& g, const int* nsplit,
+                           hipStream_t s);
 
 // The fp32 contractions (csrc/nf_wide.h): the problems of g, all of epilogue
 // epi, problem q in nsplit[q] pieces (one problem unless epi is
-// EPI_DW_PARTIAL).  a_vec: A's rows allow 16-byte loads (forward only; B's
+// EPI_DW_PARTIAL or EPI_DW_SGD).  a_vec: A's rows allow 16-byte loads (forward only; B's
 // always must there, and the tendencies read single values).  The epilogues
 // read and write rows of one pitch: ld1 (EPI_FWD_STASH) and ldaux (EPI_BWD)
 // and ldw (EPI_DW_SGD) must equal ld0.  The 256 x 256 tile takes

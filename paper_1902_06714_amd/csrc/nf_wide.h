@@ -359,7 +359,8 @@ template <int EPI>
 __device__ __forceinline__ void piece_range(const GemmParamsT<float>& p, int bz, int& kbeg, int& kend) {
   kbeg = 0;
   kend = p.K;
-  if constexpr (EPI == EPI_DW_SGD || EPI == EPI_DW_PARTIAL || EPI == EPI_FWD_PIECE) {
+  if constexpr (EPI == EPI_DW_SGD || EPI == EPI_DW_PARTIAL || EPI == EPI_FWD_PIECE ||
+                EPI == EPI_BWD_PIECE) {
     const int shard = bz / p.nsub, sub = bz % p.nsub;
     const int sb = shard * p.shard_len;
     kbeg = sb + sub * p.sub_len;
@@ -749,7 +750,7 @@ wide_kernel(const GemmGroupT<float> g, int total, int per) {
   const int b = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
   if (b >= total) return;
   int q = 0;
-  if constexpr (EPI == EPI_DW_PARTIAL) {
+  if constexpr (EPI == EPI_DW_PARTIAL || EPI == EPI_DW_SGD) {
 #pragma unroll
     for (int i = 1; i < GEMM_GROUP_MAX; ++i) q += (i < g.n && b >= g.start[i]);
   }
@@ -796,6 +797,9 @@ static hipError_t wide_dispatch(int epi, bool av, const GemmGroupT<float>& g, co
   }
   // backward: A = delta [m][k], B(k, n) = W[k][n]
   NF_CASE(EPI_BWD, true, false, true)
+  if constexpr (BM < 256) {
+    NF_CASE(EPI_BWD_PIECE, true, false, true)
+  }
   // tendencies: A(m, k) = delta[k][m], B(k, n) = activations[k][n], read one
   // value at a time, so any row pitch will do
   NF_CASE(EPI_DW_SGD, false, false, true)

@@ -10,8 +10,8 @@ hipError_t launch_wide256(int epi, bool av, const GemmGroupT<float>& g, const in
 hipError_t launch_wide(int epi, int tile, bool a_vec, const GemmGroupT<float>& g, const int* nsplit,
                        hipStream_t s) {
   const bool tendency = epi == EPI_DW_SGD || epi == EPI_DW_PARTIAL;
-  const bool forward = !tendency && epi != EPI_BWD;
-  if (g.n < 1 || g.n > (epi == EPI_DW_PARTIAL ? GEMM_GROUP_MAX : 1)) return hipErrorInvalidValue;
+  const bool forward = !tendency && epi != EPI_BWD && epi != EPI_BWD_PIECE;
+  if (g.n < 1 || g.n > (tendency ? GEMM_GROUP_MAX : 1)) return hipErrorInvalidValue;
   for (int q = 0; q < g.n; ++q) {
     const GemmParamsT<float>& p = g.p[q];
     if (p.M <= 0 || p.N <= 0 || p.K <= 0 || nsplit[q] <= 0) return hipErrorInvalidValue;
@@ -24,12 +24,12 @@ hipError_t launch_wide(int epi, int tile, bool a_vec, const GemmGroupT<float>& g
     if ((epi == EPI_FWD_STASH && p.ld1 != p.ld0) || (epi == EPI_BWD && p.ldaux != p.ld0) ||
         (epi == EPI_DW_SGD && p.ldw != p.ld0))
       return hipErrorInvalidValue;
-    if (tendency || epi == EPI_FWD_PIECE) {
+    if (tendency || epi == EPI_FWD_PIECE || epi == EPI_BWD_PIECE) {
       if (p.nsub <= 0 || nsplit[q] % p.nsub != 0) return hipErrorInvalidValue;
       // A piece of a k-contiguous operand read 16 bytes at a time must start
       // on a whole stage (nf_split.h).  The tendencies split the batch,
       // which is not the contiguous index of either of their operands.
-      if (forward && !k_pieces_aligned(nsplit[q] / p.nsub, p.shard_len, p.nsub, p.sub_len))
+      if (!tendency && !k_pieces_aligned(nsplit[q] / p.nsub, p.shard_len, p.nsub, p.sub_len))
         return hipErrorInvalidValue;
     } else if (nsplit[q] != 1) {
       return hipErrorInvalidValue;
