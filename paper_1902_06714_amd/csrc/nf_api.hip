@@ -74,6 +74,12 @@ constexpr int dtype_of() {
   return sizeof(T) == 8 ? nf::DT_F64 : nf::DT_F32;
 }
 
+// The cut of the skinny forward kernel: k pieces, and samples per workgroup.
+struct SkinnyFwdPlan {
+  nf::KSplit ks{0, 0};
+  int rows = 128;
+};
+
 }  // namespace
 
 struct nf_net {
@@ -121,6 +127,10 @@ struct nf_net {
   void* staging = nullptr;
   int64_t slot_bytes = 0;
   int slots = 0;
+  // medium nets: layer 1's plan for the last batch size (a plan takes about a
+  // microsecond to make, a small step's launches five)
+  int64_t skinny_batch = 0;
+  SkinnyFwdPlan skinny_plan;
   hipStream_t last = nullptr;
   bool used = false;
   // samples whose f'(z_l), l < L, the last training step left in fbuf (0 when
@@ -463,40 +473,49 @@ nf::KSplit fwd_split(const nf_net* n, int64_t M, int64_t N, int64_t K, bool smal
 }
 
 // The k pieces of the skinny forward kernel (layers of at most
-// SKINNY_MAX_UNITS units): one workgroup per (128 samples, piece) holding the
-// piece's slice of W in LDS, one workgroup per CU.  Among the piece counts
-// whose slice fits in LDS, the one with the fewest k-groups on the busiest
-// CU wins, the smaller on ties; nsplit 0 when none fits.
-nf::KSplit fwd_skinny_split(const nf_net* n, int64_t M, int64_t N, int64_t K) {
-  const int64_t ncu = n->ncu > 0 ? n->ncu : 256;
-  const int64_t groups = (M + 127) / 128;
-  nf::KSplit best{0, 0};
-  int64_t best_cost = -1;
+// SKINNY_MAX_UNITS units) and the samples of a workgroup (one per CU).
+// Among the piece counts whose W is at most 160 KB in fp32 (two slices of its
+// parts in LDS) and up to the one with the fewest k-groups on the busiest CU
+// at 128 samples, the least time of the two launches: a k-group of 32 inputs
+// costs the forward kernel about 0.15 us for its W and, at 128 samples, 0.1
+// per unit block of products; a piece past the second costs the per-sample
+// kernel about 0.6 us (it loads two ahead).
+SkinnyFwdPlan fwd_skinny_plan(const nf_net* n, int64_t M, int64_t N, int64_t K) {
+  const int64_t ncu = device_cus(n);
+  const int64_t blocks = (N + 15) / 16;
+  nf::KSplit cuts[16];
+  int count = 0, most = -1;
+  int64_t least = -1;
   for (int want = 1; want <= 16; ++want) {
     const nf::KSplit ks = nf::k_split(K, want);
-    if (nf::fwd_skinny_lds_bytes((int)N, ks.sub_len) > nf::SKINNY_FWD_LDS) continue;
-    const int64_t per_cu = (groups * ks.nsplit + ncu - 1) / ncu;
-    const int64_t cost = per_cu * ((ks.sub_len + 15) / 16);
-    if (best_cost < 0 || cost < best_cost) {
-      best = ks;
-      best_cost = cost;
+    const int64_t quads = 4 * ((ks.sub_len + 15) / 16);
+    if (16 * blocks * (quads % 2 == 1 ? quads : quads + 1) * 16 + 16 > 160 * 1024) continue;
+    const int64_t per_cu = ((M + 127) / 128 * ks.nsplit + ncu - 1) / ncu;
+    const int64_t steps = per_cu * ((ks.sub_len + 15) / 16);
+    cuts[count] = ks;
+    if (least < 0 || steps < least) {
+      least = steps;
+      most = count;
     }
+    ++count;
   }
+  SkinnyFwdPlan best;
+  double cost = 0.0;
+  for (int i = 0; i <= most; ++i)
+    for (int rows : {128, 32}) {
+      const nf::KSplit& ks = cuts[i];
+      const int64_t per_cu = ((M + rows - 1) / rows * ks.nsplit + ncu - 1) / ncu;
+      const double group = 0.15 + (rows == 128 ? 0.1 * (double)blocks : 0.1 * (double)((blocks + 3) / 4));
+      const double c = (double)per_cu * (2.0 + group * (double)((ks.sub_len + 31) / 32)) +
+                       0.6 * (double)std::max(0, ks.nsplit - 2);
+      if (best.ks.nsplit == 0 || c < cost) {
+        best.ks = ks;
+        best.rows = rows;
+        cost = c;
+      }
+    }
   return best;
 }
-
-// layer 1 of the medium path goes to the skinny forward kernel
-template <class T>
-bool medium_fwd_skinny(const nf_net* n, const T* x, int64_t batch) {
-  if constexpr (sizeof(T) != 4) {
-    return false;
-  } else {
-    const LayerLayout& l1 = n->layers[1];
-    return l1.out <= nf::SKINNY_MAX_UNITS && vec_ok(x, n->dims[0]) &&
-           fwd_skinny_split(n, batch, l1.out, l1.in).nsplit > 0;
-  }
-}
-
 // elements of the pieces of a forward contraction cut into nsplit pieces
 int64_t fwd_piece_elems(int64_t M, int64_t N, int nsplit) {
   return nsplit <= 1 ? 0 : nsplit * round_up(M * round_up(N, 4), kAlign);
@@ -835,7 +854,10 @@ nf_status run_backward_update(nf_net* n, const T* x, int64_t batch, double eta, 
       for (size_t j = 0; j < pieces.size() && g.n < nf::GEMM_GROUP_MAX; ++j) {
         const Piece& pj = pieces[j];
         const nf::GemmParamsT<T> p = piece_params(pj);
-        if (p.M > nf::SKINNY_MAX_UNITS || !vec_ok(p.A, p.lda) || !vec_ok(p.B, p.ldb)) continue;
+        // (the fp32 kernel reads input rows of any pitch)
+        if (p.M > nf::SKINNY_MAX_UNITS || !vec_ok(p.A, p.lda) ||
+            (sizeof(T) == 8 ? !vec_ok(p.B, p.ldb) : (reinterpret_cast<uintptr_t>(p.B) & 3) != 0))
+          continue;
         const int nsplit = shards * pj.nsub;
         g.npieces[g.n] = nsplit;
         g.p[g.n++] = p;
@@ -1109,8 +1131,9 @@ bool medium_layout(const nf_net* n, int64_t batch, nf::MediumParamsT<T>* p) {
   return off <= (sizeof(T) == 4 ? nf::MEDIUM_LDS_WEIGHTS : nf::MEDIUM64_LDS_WEIGHTS);
 }
 
+// (out: inference into it, without the deltas)
 template <class T>
-nf_status medium_forward_deltas(nf_net* n, const T* x, const T* y, int64_t batch,
+nf_status medium_forward_deltas(nf_net* n, const T* x, const T* y, int64_t batch, T* out,
                                 hipStream_t s) {
   nf::MediumParamsT<T> mp{};
   if (!medium_layout<T>(n, batch, &mp)) return fail(NF_EINVAL, "internal: not a medium net");
@@ -1127,8 +1150,16 @@ nf_status medium_forward_deltas(nf_net* n, const T* x, const T* y, int64_t batch
   p.M = (int)batch;
   p.N = l1.out;
   p.K = l1.in;
-  const bool skinny = medium_fwd_skinny<T>(n, x, batch);
-  const nf::KSplit ks = skinny ? fwd_skinny_split(n, p.M, p.N, p.K) : fwd_split(n, p.M, p.N, p.K, false);
+  // fp32 takes the skinny forward kernel, whatever the input rows' pitch
+  bool skinny = false;
+  if (sizeof(T) == 4 && l1.out <= nf::SKINNY_MAX_UNITS && (reinterpret_cast<uintptr_t>(x) & 3) == 0) {
+    if (n->skinny_batch != batch) {
+      n->skinny_plan = fwd_skinny_plan(n, p.M, p.N, p.K);
+      n->skinny_batch = batch;
+    }
+    skinny = n->skinny_plan.ks.nsplit > 0;
+  }
+  const nf::KSplit ks = skinny ? n->skinny_plan.ks : fwd_split(n, p.M, p.N, p.K, false);
   const int sub_len = ks.sub_len;
   const int nsplit = ks.nsplit;
   const int64_t ldz = round_up(p.N, 4);
@@ -1144,7 +1175,9 @@ nf_status medium_forward_deltas(nf_net* n, const T* x, const T* y, int64_t batch
   if constexpr (sizeof(T) == 4) {
     if (skinny) {
       st = timed(n, "fwd_skinny", gemm_bytes(nf::EPI_FWD_PIECE, p.M, p.N, p.K, nsplit, 4.0),
-                 2.0 * p.M * (double)p.N * p.K, s, [&] { return nf::launch_fwd_skinny(p, s); });
+                 2.0 * p.M * (double)p.N * p.K, s, [&] {
+                   return nf::launch_fwd_skinny(p, n->skinny_plan.rows, s);
+                 });
       if (st != NF_OK) return st;
     }
   }
@@ -1162,6 +1195,7 @@ nf_status medium_forward_deltas(nf_net* n, const T* x, const T* y, int64_t batch
   mp.ldz = ldz;
   mp.np = nsplit;
   mp.Y = y;
+  mp.out = out;
   const double es = (double)sizeof(T);
   double by = es * ((double)nsplit * batch * p.N + (double)batch * n->dims[L]), fl = 0.0;
   for (int l = 1; l <= L; ++l) {
@@ -1173,10 +1207,14 @@ nf_status medium_forward_deltas(nf_net* n, const T* x, const T* y, int64_t batch
     mp.A[l - 1] = as<T>(n->actv[l]);
     mp.D[l - 1] = as<T>(n->dbuf[l]);
     mp.lda[l - 1] = ly.lda;
-    by += es * ((double)batch * ly.out * (l < L ? 2 : 1) + (l >= 2 ? (double)ly.out * ly.in : 0));
-    if (l >= 2) fl += 4.0 * batch * (double)ly.out * ly.in;   // forward and delta products
+    by += es * ((out ? 0.0 : (double)batch * ly.out * (l < L ? 2 : 1)) +
+                (l >= 2 ? (double)ly.out * ly.in : 0));
+    // forward and delta products
+    if (l >= 2) fl += (out ? 2.0 : 4.0) * batch * (double)ly.out * ly.in;
   }
-  return timed(n, sizeof(T) == 4 ? "medium_fwd_deltas" : "medium64_fwd_deltas", by, fl, s,
+  const char* name = sizeof(T) == 4 ? (out ? "medium_infer" : "medium_fwd_deltas")
+                                    : (out ? "medium64_infer" : "medium64_fwd_deltas");
+  return timed(n, name, by, fl, s,
                [&] { return nf::launch_medium(mp, n->ncu > 0 ? n->ncu : 256, s); });
 }
 
@@ -1192,7 +1230,7 @@ nf_status train_step(nf_net* n, const T* x, const T* y, int64_t batch, double et
   if (narrow) {
     st = narrow_train_step<T>(n, x, y, batch, eta, s);
   } else if (medium_layout<T>(n, batch, &mp)) {
-    st = medium_forward_deltas<T>(n, x, y, batch, s);
+    st = medium_forward_deltas<T>(n, x, y, batch, nullptr, s);
     if (st == NF_OK) st = run_backward_update<T>(n, x, batch, eta, shards, s, true);
   } else {
     st = run_forward<T>(n, x, y, batch, nullptr, true, s);
@@ -1229,6 +1267,11 @@ nf_status infer(nf_net* n, const T* x, int64_t batch, T* out, hipStream_t s) {
       return timed(n, nf::narrow64_fwd_name(false, fp), by, fl, s,
                    [&] { return nf::launch_narrow64_fwd(false, fp, s); });
   }
+  // two launches, where a launch a layer and the fold of layer 1's pieces
+  // took five for three layers (784-116-46-41-12 at 505 samples: 29.3 us, 18.2)
+  nf::MediumParamsT<T> mp{};
+  if (medium_layout<T>(n, batch, &mp))
+    return medium_forward_deltas<T>(n, x, nullptr, batch, out, s);
   return run_forward<T>(n, x, nullptr, batch, out, false, s);
 }
 
@@ -1610,7 +1653,7 @@ int64_t partial_need(const nf_net* n, const T* x, int64_t batch, int shards) {
     const nf::KSplit ks = fwd_split(n, batch, l1.out, l1.in, false);
     int np = ks.nsplit;
     if (n->dtype == nf::DT_F32 && l1.out <= nf::SKINNY_MAX_UNITS)
-      np = std::max(np, fwd_skinny_split(n, batch, l1.out, l1.in).nsplit);
+      np = std::max(np, fwd_skinny_plan(n, batch, l1.out, l1.in).ks.nsplit);
     need = std::max(need, np * round_up(batch * round_up(l1.out, 4), kAlign));
   } else {
     for (int l = 1; l <= num_layers(n); ++l) {

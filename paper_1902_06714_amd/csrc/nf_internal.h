@@ -178,17 +178,14 @@ hipError_t launch_dw_skinny_group64(SkinnyGroup64 g, hipStream_t s);
 // inputs per workgroup tile of the fp32 and fp64 tendency kernels
 constexpr int SKINNY_TILE_F32 = 64, SKINNY_TILE_F64 = 32;
 
-// Forward pieces of a fp32 layer of at most SKINNY_MAX_UNITS units (N),
-// operands loaded straight into the matrix cores (csrc/nf_skinny.hip):
-// partial[piece][m][ld0] = sum over k in piece of A[m][k] B[n][k], pieces
-// of sub_len inputs (a multiple of 16 when nsub > 1), nsub of them; A rows
-// (lda) and B rows (ldb) 16-byte aligned with K and both pitches multiples
-// of 4.  A workgroup holds the piece's slice of B in LDS:
-// fwd_skinny_lds_bytes(N, sub_len) must not exceed SKINNY_FWD_LDS.
-constexpr int SKINNY_FWD_PD = 8;          // k-groups of sample loads in flight
+// Forward pieces of a fp32 layer of at most SKINNY_MAX_UNITS units (N) on the
+// bf16 matrix cores (csrc/nf_skinny.hip): partial[piece][m][ld0] = sum over k in
+// piece of A[m][k] B[n][k], pieces of sub_len inputs (a multiple of 16 when
+// nsub > 1), nsub of them; B rows (ldb) 16-byte aligned and zero from K to a
+// whole vector; A rows of any pitch.  rows: samples per workgroup, 128 or 32.
+constexpr int SKINNY_FWD_PD = 4;          // k-groups of sample loads in flight
 constexpr int SKINNY_FWD_LDS = 160 * 1024;
-int64_t fwd_skinny_lds_bytes(int N, int sub_len);
-hipError_t launch_fwd_skinny(const GemmParamsT<float>& p, hipStream_t s);
+hipError_t launch_fwd_skinny(const GemmParamsT<float>& p, int rows, hipStream_t s);
 
 // Fold the per-piece tendencies of up to FOLD_GROUP_MAX layers in piece order,
 // store each sum as the tendency, and write the SGD step W = Win - scale * G,
@@ -352,6 +349,7 @@ struct MediumParamsT {
   const T* Y;                              // targets [B][d_L]
   T* A[MEDIUM_MAX_LAYERS];                 // f(z_l) [B][lda_l], l = 1..L-1
   T* D[MEDIUM_MAX_LAYERS];                 // delta_l [B][lda_l], l = 1..L
+  T* out;                                  // inference: f(z_L) [B][d_L] (null: training)
   int64_t lda[MEDIUM_MAX_LAYERS];
   // W_l, l >= 2, in LDS at woff[l-1] as wrows[l-1] = round_up(d_l, 16) rows
   // of wp[l-1] elements (round_up(d_{l-1}, 16) plus bank padding, 18 mod 32),

@@ -105,7 +105,8 @@ __device__ __forceinline__ void with_act(int act, F&& f) {
 
 }  // namespace
 
-template <class T, int NSB, int L>
+// TRAIN false: inference, which writes f(z_L) to p.out and stores nothing else.
+template <class T, int NSB, int L, bool TRAIN>
 __global__ void __launch_bounds__(M_THREADS) medium_kernel(const MediumParamsT<T> p) {
   using M = MedT<T>;
   constexpr int TS = 16 * NSB;                       // samples per tile
@@ -168,6 +169,7 @@ __global__ void __launch_bounds__(M_THREADS) medium_kernel(const MediumParamsT<T
     }
   };
   auto load_y = [&](int tt) {
+    if constexpr (!TRAIN) return;
     const int rem = p.B - tt * TS, tc = tt < ntiles ? tt : ntiles - 1;
 #pragma unroll
     for (int jj = 0; jj < NJ; ++jj) {
@@ -253,7 +255,8 @@ __global__ void __launch_bounds__(M_THREADS) medium_kernel(const MediumParamsT<T
           T a, f;
           act_eval(decltype(act)::value, zs[jj][v] + b1r[jj], a, f);
           a = ok ? a : T(0);
-          M::store(a, ares, ok ? vb : MEDIUM_OOB, SZ * (unsigned)((s0 + RS * v) * lda));
+          if constexpr (TRAIN)
+            M::store(a, ares, ok ? vb : MEDIUM_OOB, SZ * (unsigned)((s0 + RS * v) * lda));
           hs[0][rw + RS * v][u] = a;
           fp[0][jj][v] = f;
         }
@@ -397,8 +400,8 @@ __global__ void __launch_bounds__(M_THREADS) medium_kernel(const MediumParamsT<T
       const int N = p.dims[l], K = (p.dims[l - 1] + 3) & ~3;
       const int wp = p.wp[l - 1];
       const T* w = wl + p.woff[l - 1];
-      const __amdgpu_buffer_rsrc_t ores = rsrc(l < L ? p.A[l - 1] : p.D[l - 1]);
-      const int lda = (int)p.lda[l - 1];
+      const __amdgpu_buffer_rsrc_t ores = rsrc(!TRAIN ? p.out : l < L ? p.A[l - 1] : p.D[l - 1]);
+      const int lda = TRAIN ? (int)p.lda[l - 1] : dL;
       with_act(p.acts[l - 1], [&](auto act) {
 #pragma unroll
         for (int jj = 0; jj < NJ; ++jj) {
@@ -415,9 +418,11 @@ __global__ void __launch_bounds__(M_THREADS) medium_kernel(const MediumParamsT<T
             act_eval(decltype(act)::value, acc[v] + b, a, f);
             if (l < L) {
               a = ok ? a : T(0);
-              M::store(a, ores, ok ? vb : MEDIUM_OOB, so);
+              if constexpr (TRAIN) M::store(a, ores, ok ? vb : MEDIUM_OOB, so);
               hs[cur ^ 1][rw + RS * v][u] = a;
               fp[l - 1][jj][v] = f;
+            } else if constexpr (!TRAIN) {
+              M::store(a, ores, ok ? vb : MEDIUM_OOB, so);
             } else {
               const T d = ok ? (a - py[jj][v]) * f : T(0);
               M::store(d, ores, ok ? vb : MEDIUM_OOB, so);
@@ -429,6 +434,13 @@ __global__ void __launch_bounds__(M_THREADS) medium_kernel(const MediumParamsT<T
       if (l == L) load_y(t + gridDim.x);
       cur ^= 1;
       __syncthreads();
+    }
+
+    if constexpr (!TRAIN) {
+      // layer L's barrier has passed, so the next tile's layer 1 may write
+      // buffer 0, and its layer 2 reads it
+      cur = 0;
+      continue;
     }
 
     // ---- hidden deltas, l = L-1 .. 1: (W_{l+1}^T delta_{l+1}) * f'(z_l).
@@ -473,30 +485,35 @@ static int medium_tile_blocks(int B, int ncu, int esz) {
   return nsb < 1 ? 1 : nsb > 3 ? 3 : nsb;
 }
 
-template <class T, int NSB>
+template <class T, int NSB, bool TRAIN>
 static hipError_t launch_nsb(const MediumParamsT<T>& p, dim3 grid, hipStream_t s) {
   switch (p.L) {
-    case 2: return launch_k(medium_kernel<T, NSB, 2>, grid, M_THREADS, 0, s, p);
-    case 3: return launch_k(medium_kernel<T, NSB, 3>, grid, M_THREADS, 0, s, p);
-    default: return launch_k(medium_kernel<T, NSB, 4>, grid, M_THREADS, 0, s, p);
+    case 2: return launch_k(medium_kernel<T, NSB, 2, TRAIN>, grid, M_THREADS, 0, s, p);
+    case 3: return launch_k(medium_kernel<T, NSB, 3, TRAIN>, grid, M_THREADS, 0, s, p);
+    default: return launch_k(medium_kernel<T, NSB, 4, TRAIN>, grid, M_THREADS, 0, s, p);
   }
 }
 
-template <class T>
-hipError_t launch_medium(const MediumParamsT<T>& p, int ncu, hipStream_t s) {
+template <class T, bool TRAIN>
+static hipError_t launch_mode(const MediumParamsT<T>& p, int ncu, hipStream_t s) {
   if (p.L < 2 || p.L > MEDIUM_MAX_LAYERS) return hipErrorInvalidValue;
   const int nsb = medium_tile_blocks(p.B, ncu, (int)sizeof(T));
   const int ntiles = (p.B + 16 * nsb - 1) / (16 * nsb);
   const dim3 grid(ntiles < ncu ? ntiles : ncu);
   if constexpr (sizeof(T) == 8) {
-    return launch_nsb<T, 1>(p, grid, s);
+    return launch_nsb<T, 1, TRAIN>(p, grid, s);
   } else {
     switch (nsb) {
-      case 1: return launch_nsb<T, 1>(p, grid, s);
-      case 2: return launch_nsb<T, 2>(p, grid, s);
-      default: return launch_nsb<T, 3>(p, grid, s);
+      case 1: return launch_nsb<T, 1, TRAIN>(p, grid, s);
+      case 2: return launch_nsb<T, 2, TRAIN>(p, grid, s);
+      default: return launch_nsb<T, 3, TRAIN>(p, grid, s);
     }
   }
+}
+
+template <class T>
+hipError_t launch_medium(const MediumParamsT<T>& p, int ncu, hipStream_t s) {
+  return p.out ? launch_mode<T, false>(p, ncu, s) : launch_mode<T, true>(p, ncu, s);
 }
 
 template hipError_t launch_medium<float>(const MediumParamsT<float>&, int, hipStream_t);

@@ -1,0 +1,51 @@
+// An fp32 value as three bf16 values, for products on the bf16 matrix cores.
+//
+// x = h + m + l to its last bit, h = bf16(x), m = bf16(x - h), l = bf16(x - h -
+// m), each rounded to nearest, so |m| <= 2^-9 |x| and |l| <= 2^-18 |x|.  A
+// product a b is formed as the six products hh, hm, mh, mm, hl, lh, each exact
+// (8 x 8 significand bits), accumulated in fp32; what is left out (ml, lm,
+// ll) is below 2^-25 |a b|.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+namespace nf {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ unsigned pack_bf16(float a, float b) {
+  const floatx2 f = {a, b};
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(f, bf16x2));
+}
+
+// The three bf16 parts of two values, packed (a in the low half).
+__device__ __forceinline__ void split3(float a, float b, unsigned& h, unsigned& m, unsigned& l) {
+  h = pack_bf16(a, b);
+  const float a1 = a - __builtin_bit_cast(float, h << 16);
+  const float b1 = b - __builtin_bit_cast(float, h & 0xffff0000u);
+  m = pack_bf16(a1, b1);
+  l = pack_bf16(a1 - __builtin_bit_cast(float, m << 16),
+                b1 - __builtin_bit_cast(float, m & 0xffff0000u));
+}
+
+// The six products by part (0 h, 1 m, 2 l) of A and of B, the small ones first.
+constexpr int PART_A[6] = {2, 0, 1, 1, 0, 0}, PART_B[6] = {0, 2, 1, 0, 1, 0};
+
+// Whether a sum of six products cannot be trusted.  An operand that is not
+// finite, or that rounds to infinity in bf16, leaves a NaN or an infinity in
+// every sum it enters; operands so small that their last parts are below the
+// smallest normal number, which the matrix cores read as zeros, leave a tiny
+// sum.  Such sums are formed again on the fp32 matrix cores.
+constexpr float PARTS_TINY = 8.271806e-25f;   // 2^-80
+__device__ __forceinline__ bool parts_doubtful(float sum) {
+  const float c = fabsf(sum);
+  return !(c < __builtin_inff()) || (c > 0.f && c < PARTS_TINY);
+}
+
+}  // namespace nf

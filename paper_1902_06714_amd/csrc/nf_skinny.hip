@@ -39,10 +39,9 @@
 #include <atomic>
 
 #include "nf_internal.h"
+#include "nf_parts.h"
 
 namespace nf {
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 namespace {
 
@@ -58,8 +57,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t sk_rsrc(const float* base) {
 __device__ __forceinline__ floatx4 sk_load(__amdgpu_buffer_rsrc_t rs, unsigned off) {
   return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
 }
-
-typedef float floatx2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ floatx2 sk_load2(__amdgpu_buffer_rsrc_t rs, unsigned off) {
   return __builtin_bit_cast(floatx2, __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0));
@@ -112,6 +109,27 @@ struct SkSide {
     if (b < 4 * S4 + 2 * S2) return g.v2[b - 4 * S4];
     return g.v1;
   }
+};
+
+// The last tile of rows that are not whole 16-byte vectors: NB blocks of 16
+// rows, row 16 b + r of block b, read one value at a time (a vector would
+// reach past the row's end, which may be the end of the allocation).
+template <int NBLK>
+struct SkSideOdd {
+  static constexpr int NB = NBLK, B2 = 0;
+  __device__ static int row(int b, int r) { return 16 * b + r; }
+  struct Regs {
+    float v[NBLK];
+  };
+  __device__ static void load(Regs& g, __amdgpu_buffer_rsrc_t rs, unsigned base, int r, int lim,
+                              bool ok) {
+#pragma unroll
+    for (int b = 0; b < NBLK; ++b) {
+      const int e = 16 * b + r;
+      g.v[b] = sk_load1(rs, ok && e < lim ? base + 4u * (unsigned)e : SK_OOB);
+    }
+  }
+  __device__ static float at(const Regs& g, int b) { return g.v[b]; }
 };
 
 // One workgroup's (piece, input tile): unit side U against input side X.
@@ -252,13 +270,17 @@ __device__ __forceinline__ void skinny_tile(const GemmParamsT<float>& p, int pie
         ((bred[0][tid] + bred[1][tid]) + bred[2][tid]) + bred[3][tid];
 }
 
-// the tile's input side: a whole tile of 64 inputs, or the last tile's
-// ceil(rest / 16) blocks
+// the tile's input side: a whole tile of 64 inputs, or the last tile's nx =
+// ceil(rest / 16) blocks, 4 + nx where its rows are not whole vectors
 template <class U>
 __device__ __forceinline__ void skinny_tile_x(const GemmParamsT<float>& p, int piece, int tile,
                                               int nx, floatx4 (*red)[16][64],
                                               float (*bred)[SKINNY_MAX_UNITS]) {
   switch (nx) {
+    case 5: skinny_tile<U, SkSideOdd<1>>(p, piece, tile, red, bred); break;
+    case 6: skinny_tile<U, SkSideOdd<2>>(p, piece, tile, red, bred); break;
+    case 7: skinny_tile<U, SkSideOdd<3>>(p, piece, tile, red, bred); break;
+    case 8: skinny_tile<U, SkSideOdd<4>>(p, piece, tile, red, bred); break;
     case 1: skinny_tile<U, SkSide<0, 0, 1>>(p, piece, tile, red, bred); break;
     case 2: skinny_tile<U, SkSide<0, 1, 0>>(p, piece, tile, red, bred); break;
     case 3: skinny_tile<U, SkSide<0, 1, 1>>(p, piece, tile, red, bred); break;
@@ -284,7 +306,8 @@ __global__ void __launch_bounds__(SK_NT, 2) skinny_dw_kernel(const SkinnyGroup g
   const int tile = slot % ntile;
   if (piece >= g.npieces[q]) return;
   const int rest = p.N - tile * SK_TN;
-  const int nx = rest >= SK_TN ? 4 : (rest + 15) >> 4;
+  const bool vec = (p.ldb & 3) == 0 && (reinterpret_cast<uintptr_t>(p.B) & 15) == 0;
+  const int nx = rest >= SK_TN ? 4 : ((rest + 15) >> 4) + (vec ? 0 : 4);
   switch ((p.M + 15) >> 4) {
     case 1: skinny_tile_x<SkSide<0, 0, 1>>(p, piece, tile, nx, red, bred); break;
     case 2: skinny_tile_x<SkSide<0, 1, 0>>(p, piece, tile, nx, red, bred); break;
@@ -513,185 +536,265 @@ __global__ void __launch_bounds__(SK_NT, 2) skinny_dw64_kernel(const SkinnyGroup
 // ---------------------------------------------------------------------------
 // Forward pieces of a layer of at most SKINNY_MAX_UNITS units (section 3.2:
 // z[s][u] = sum over inputs n of x[s][n] W[u][n], over one piece of the
-// input range).  The k index is contiguous in both operands, so lane (r, g)
-// takes inputs k0 + 4 g .. + 3 of a row in one 16-byte access and uses them
-// in the 4 products of a k-group of 16 inputs.
+// input range), on the bf16 matrix cores with three parts per operand
+// (nf_parts.h).  The k index is contiguous in both operands, so lane (r, g) of
+// a 16x16x32 product takes inputs k0 + 8 g .. + 7 of a row.
 //
-// A workgroup of 8 waves owns one piece and 8 blocks of 16 samples.  It
-// copies the piece's slice of W (every unit, the piece's inputs) into LDS,
-// at a row pitch of 4 (odd) floats so that the 16 rows of a fragment read
-// fall on distinct banks, in two parts: the first SKINNY_FWD_PD k-groups
-// (when the piece has at least twice as many), then the rest, whose loads
-// are in flight while the first part's products run.  After each part's
-// barrier every wave runs its own sample block: the sample rows come from
-// global memory, SKINNY_FWD_PD k-groups ahead, the unit rows from LDS.
+// A workgroup of 8 waves owns one piece and 8 blocks of 16 samples, or, where
+// those would leave most CUs idle, 2 blocks of which 4 waves each take a
+// quarter of the units.  It
+// holds the parts of W (every unit, as many k-groups of 32 inputs as fit:
+// skf_groups) in LDS, [part][8 inputs][unit][8] with the groups of 8 inputs 32
+// bytes further apart, so that the lanes that write 4 such groups of 2 units
+// at once, and the 16 units of a read, fall on distinct banks.  A longer
+// piece takes the next slice of W after a barrier; the slice's first loads
+// are in flight meanwhile.  Every wave runs its own sample block: the sample
+// rows come from global memory, SKINNY_FWD_PD k-groups ahead, and are split
+// in registers; the unit rows come from LDS.  The hh products and the small
+// ones have accumulators of their own.
+//
+// Rows of x may start at any 4-byte address (the hardware takes 16-byte loads
+// there); where they are not whole 16-byte vectors the last, partial k-group
+// is read one value at a time, since the row's end may be the end of the
+// allocation.
+//
+// A large batch is bound by the matrix products and by the LDS reads of W's
+// parts, which every wave makes for its own samples (784 -> 100 units, 10000
+// samples, 16 shards: 24.7 us with fp32 products, 20.7 so); a small one by the
+// first loads and the copy of W (784 -> 100 units: 6 - 12 us by batch, 4 - 9).
 // ---------------------------------------------------------------------------
 constexpr int SKF_NT = 512;    // 8 waves
-constexpr int SKF_BATCH = 8;   // 16-byte copy loads per thread in one round
+constexpr int SKF_BATCH = 4;   // chunks of 8 inputs that a thread loads in one round
 
-// the 16-byte chunks of one round of the copy: values and LDS offsets
-struct SkfChunks {
-  floatx4 v[SKF_BATCH];
-  int at[SKF_BATCH];
+template <int NUB>
+struct SkfLayout {
+  static constexpr int UNITS = 16 * NUB;
+  static constexpr int OCT = UNITS * 16 + 32;   // bytes of 8 inputs of every unit
+  static constexpr int GROUP = 4 * OCT;         // bytes of a k-group of one part
 };
 
-template <int NUB, class Stage>
-__device__ __forceinline__ void fwd_skinny_tile(const GemmParamsT<float>& p, int sblk, int piece,
-                                                const float* ws, int pk, Stage& stage) {
+// one thread's chunks of a round: 8 inputs of one unit each
+struct SkfChunks {
+  float v[SKF_BATCH][8];
+};
+
+// WU waves share a block of 16 samples, each with its share of the unit blocks.
+template <int NUB, int WU>
+__device__ __forceinline__ void fwd_skinny_tile(const GemmParamsT<float>& p, int group, int piece,
+                                                char* ws, int slice) {
+  typedef SkfLayout<NUB> LY;
+  constexpr int NW = (NUB + WU - 1) / WU;      // unit blocks of a wave
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int sblk = group * (SKF_NT / 64 / WU) + wave / WU;
+  const int ub = wave % WU * NW;               // this wave's first unit block
   const int lane = threadIdx.x & 63;
   const int r = lane & 15, gq = lane >> 4;
-  const int M = p.M, N = p.N;
+  const int M = p.M, N = p.N, K = p.K;
   const int s0 = 16 * sblk;
   const int kbeg = piece * p.sub_len;
-  const int kend = min(kbeg + p.sub_len, p.K);
-  const int ngr = kend > kbeg ? (kend - kbeg + 15) >> 4 : 0;   // k-groups of 16 inputs
+  const int kend = min(kbeg + p.sub_len, K);
+  const int ngr = kend > kbeg ? (kend - kbeg + 31) >> 5 : 0;   // k-groups of 32 inputs
   const bool xok = s0 + r < M;
-  const __amdgpu_buffer_rsrc_t ra = sk_rsrc(p.A + (int64_t)s0 * p.lda);
-  const int lda = (int)p.lda;
+  const int lda = (int)p.lda, ldb = (int)p.ldb;
+  const __amdgpu_buffer_rsrc_t ra = sk_rsrc(p.A + (int64_t)s0 * p.lda + kbeg);
+  const __amdgpu_buffer_rsrc_t rb = sk_rsrc(p.B + kbeg);
+  const bool vec = (lda & 3) == 0 && (reinterpret_cast<uintptr_t>(p.A) & 15) == 0;
+  const int part = slice * LY::GROUP;          // bytes of one part of a slice
 
-  floatx4 acc[NUB];
+  floatx4 acc[NW], small[NW];
 #pragma unroll
-  for (int u = 0; u < NUB; ++u) acc[u] = floatx4{0.f, 0.f, 0.f, 0.f};
-  // k-group t: inputs kbeg + 16 t + 4 gq .. + 3 (whole vectors: the pieces
-  // start on multiples of 16 and the row length is a multiple of 4)
-  auto load = [&](int t) {
-    const int k = kbeg + 16 * t + 4 * gq;
-    return sk_load(ra, k < kend && xok ? 4u * (unsigned)(r * lda + k) : SK_OOB);
+  for (int u = 0; u < NW; ++u) acc[u] = small[u] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+  // the 8 values of this lane's sample row in k-group t
+  struct Row {
+    floatx4 v[2];
   };
-  const float* wl = ws + r * pk + 4 * gq;
-  auto step = [&](const floatx4& xv, int t) {
-    floatx4 wv[NUB];
+  auto load = [&](Row& x, int t) {
+    const int k = 32 * t + 8 * gq, len = kend - kbeg;
+    const unsigned at = 4u * (unsigned)(r * lda + k);
+    if (vec || 32 * (t + 1) <= len || 32 * t >= len) {
 #pragma unroll
-    for (int u = 0; u < NUB; ++u)
-      wv[u] = *reinterpret_cast<const floatx4*>(wl + 16 * u * pk + 16 * t);
+      for (int h = 0; h < 2; ++h) x.v[h] = sk_load(ra, xok && k + 4 * h < len ? at + 16u * h : SK_OOB);
+    } else {
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt)
-#pragma unroll
-      for (int u = 0; u < NUB; ++u)
-        acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[tt], wv[u][tt], acc[u], 0, 0, 0);
+      for (int c = 0; c < 8; ++c)
+        x.v[c >> 2][c & 3] = sk_load1(ra, xok && k + c < len ? at + 4u * c : SK_OOB);
+    }
   };
+  // W chunks: chunk i is 8 inputs 8 (i % 4) of k-group i / (4 UNITS), unit i / 4 %
+  // UNITS, so the lanes of a quad read 128 contiguous bytes of a row (W's rows
+  // are whole vectors, zero past the last input)
+  auto issue = [&](SkfChunks& g, int g0, int g1, int q) {
+#pragma unroll
+    for (int j = 0; j < SKF_BATCH; ++j) {
+      const int i = (q * SKF_BATCH + j) * SKF_NT + (int)threadIdx.x;
+      const int u = (i >> 2) % LY::UNITS, t = g0 + (i >> 2) / LY::UNITS;
+      const int k = 32 * t + 8 * (i & 3);
+      const unsigned at = 4u * (unsigned)(u * ldb + k);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const floatx4 w = sk_load(rb, t < g1 && u < N && kbeg + k + 4 * h < kend ? at + 16u * h : SK_OOB);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) g.v[j][4 * h + c] = w[c];
+      }
+    }
+  };
+  auto store = [&](const SkfChunks& g, int g0, int g1, int q) {
+#pragma unroll
+    for (int j = 0; j < SKF_BATCH; ++j) {
+      const int i = (q * SKF_BATCH + j) * SKF_NT + (int)threadIdx.x;
+      const int u = (i >> 2) % LY::UNITS, t = (i >> 2) / LY::UNITS;
+      if (g0 + t < g1) {
+        uintx4 o[3];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          unsigned h, m, l;
+          split3(g.v[j][2 * c], g.v[j][2 * c + 1], h, m, l);
+          o[0][c] = h;
+          o[1][c] = m;
+          o[2][c] = l;
+        }
+        char* at = ws + t * LY::GROUP + (i & 3) * LY::OCT + u * 16;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) *reinterpret_cast<uintx4*>(at + a * part) = o[a];
+      }
+    }
+  };
+  auto rounds = [&](int g0, int g1) {
+    return ((g1 - g0) * 4 * LY::UNITS + SKF_BATCH * SKF_NT - 1) / (SKF_BATCH * SKF_NT);
+  };
+  // (a wave's blocks past the last read the first ones and are not stored)
+  const int frag = gq * LY::OCT + r * 16 + (ub < NUB ? ub : 0) * 256;
+  const bool idle = s0 >= M || ub >= NUB;      // only copies W
+  auto step = [&](const Row& x, int t) {       // t: k-group within the slice
+    bf16x8 a[3];
+    {
+      uintx4 o[3];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        unsigned h, m, l;
+        split3(x.v[c >> 1][2 * (c & 1)], x.v[c >> 1][2 * (c & 1) + 1], h, m, l);
+        o[0][c] = h;
+        o[1][c] = m;
+        o[2][c] = l;
+      }
+#pragma unroll
+      for (int q = 0; q < 3; ++q) a[q] = __builtin_bit_cast(bf16x8, o[q]);
+    }
+    const char* at = ws + t * LY::GROUP + frag;
+#pragma unroll
+    for (int u = 0; u < NW; ++u) {
+      bf16x8 b[3];
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+        b[q] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uintx4*>(at + q * part + (NUB % WU == 0 || ub + u < NUB ? u : 0) * 256));
+#pragma unroll
+      for (int y = 0; y < 6; ++y) {
+        floatx4& c = y == 5 ? acc[u] : small[u];
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[PART_A[y]], b[PART_B[y]], c, 0, 0, 0);
+      }
+    }
+    // the next unit block's reads before this one's products
+    __builtin_amdgcn_sched_group_barrier(0x100, NW > 1 ? 6 : 3, 0);
+#pragma unroll
+    for (int u = 0; u < NW; ++u) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);
+      if (u + 2 < NW) __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+    }
+  };
+
   constexpr int PD = SKINNY_FWD_PD;
-  const bool has_rows = s0 < M;
-  // the copy's split: k-groups [0, hs) first, 4 hs chunk columns
-  const int hs = ngr >= 2 * PD ? PD : 0;
-  // the first part's loads (from the L2) issue before the sample rows' (from
-  // memory), so that they are not queued behind them; the second part's
-  // first round follows the sample rows
-  SkfChunks g1, g2;
-  stage.issue(g1, 0, 4 * hs, 0);
-  floatx4 xv[PD];
+  SkfChunks g;
+  Row x[PD];
+  // W's loads (from the L2) before the sample rows' (from memory): a CU
+  // returns its loads in order
+  issue(g, 0, min(slice, ngr), 0);
 #pragma unroll
-  for (int d = 0; d < PD; ++d) xv[d] = load(d);
-  stage.issue(g2, 4 * hs, 4 * ngr, 0);
-  stage.store(g1);
-  stage.copy(0, 4 * hs, 1);
-  __syncthreads();
-  int t = 0;
-  if (has_rows && hs == PD) {
-#pragma unroll
-    for (int d = 0; d < PD; ++d) {
-      step(xv[d], d);
-      xv[d] = load(d + PD);
+  for (int d = 0; d < PD; ++d) load(x[d], d);
+  for (int g0 = 0; g0 < ngr; g0 += slice) {
+    const int g1 = min(g0 + slice, ngr);
+    store(g, g0, g1, 0);
+    for (int q = 1; q < rounds(g0, g1); ++q) {
+      issue(g, g0, g1, q);
+      store(g, g0, g1, q);
     }
-    t = PD;
-  }
-  stage.store(g2);
-  stage.copy(4 * hs, 4 * ngr, 1);
-  __syncthreads();
-  if (!has_rows) return;
-  for (; t + PD <= ngr; t += PD) {
+    __syncthreads();
+    if (g1 < ngr) issue(g, g1, min(g1 + slice, ngr), 0);
+    int t = g0;
+    for (; !idle && t + PD <= g1; t += PD) {
 #pragma unroll
-    for (int d = 0; d < PD; ++d) {
-      step(xv[d], t + d);
-      xv[d] = load(t + d + PD);
+      for (int d = 0; d < PD; ++d) {
+        step(x[d], t + d - g0);
+        load(x[d], t + d + PD);
+      }
+    }
+    // the slice's last k-groups; the registers then hold the next slice's
+    // first ones in order again
+    const int rest = idle ? 0 : g1 - t;
+#pragma unroll
+    for (int d = 0; d < PD - 1; ++d)
+      if (d < rest) step(x[d], t + d - g0);
+    if (g1 < ngr) {
+#pragma unroll
+      for (int d = 0; d < PD; ++d) load(x[d], g1 + d);
+      __syncthreads();
     }
   }
+
+  bool bad = false;
 #pragma unroll
-  for (int d = 0; d < PD - 1; ++d)
-    if (t + d < ngr) step(xv[d], t + d);
+  for (int u = 0; u < NW; ++u) {
+    acc[u] += small[u];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) bad |= parts_doubtful(acc[u][v]);
+  }
+  if (__any(bad)) {
+    // this wave's block again in fp32: input 4 j + g of lane (r, g)
+#pragma unroll
+    for (int u = 0; u < NW; ++u) acc[u] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int k = gq; k < ((kend - kbeg + 3) & ~3); k += 4) {
+      const bool ok = k < kend - kbeg;
+      const float a = sk_load1(ra, ok && xok ? 4u * (unsigned)(r * lda + k) : SK_OOB);
+#pragma unroll
+      for (int u = 0; u < NW; ++u) {
+        const int n = 16 * (ub + u) + r;
+        const float w = sk_load1(rb, ok && n < N ? 4u * (unsigned)(n * ldb + k) : SK_OOB);
+        acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, w, acc[u], 0, 0, 0);
+      }
+    }
+  }
 
   // accumulator register v of lane (r, gq): sample s0 + 4 gq + v, unit 16 u + r
   float* out = p.partial + (int64_t)piece * p.pstride;
 #pragma unroll
-  for (int u = 0; u < NUB; ++u)
+  for (int u = 0; u < NW; ++u)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int m = s0 + 4 * gq + v;
-      if (m < M && 16 * u + r < N) out[(int64_t)m * p.ld0 + 16 * u + r] = acc[u][v];
+      const int m = s0 + 4 * gq + v, n = 16 * (ub + u) + r;
+      if (m < M && n < N) out[(int64_t)m * p.ld0 + n] = acc[u][v];
     }
 }
 
-// The copy of a piece's slice of W: row u, inputs kbeg .. kend - 1 at
-// ws[u * pk + ..], zeros up to the end of the last k-group (their products
-// meet the zeros that the sample loads past kend return).  A part of it is
-// the chunk columns [c0, c1) (4 floats each) of every row: chunk i of the
-// part is row i / w, column c0 + i % w with w = c1 - c0, the quotient a
-// multiply-high by floor(2^32 / w) + 1, exact while i w < 2^32 (the slice
-// fits in LDS, so both stay below 2^14).  Chunks past the part go to the
-// spare 16 bytes after the slice's rows, so no store is tied to a branch.
-struct SkfStage {
-  const GemmParamsT<float>& p;
-  float* ws;
-  int pk, kbeg, kend, spare, ldb;
-  __amdgpu_buffer_rsrc_t rb;
-
-  __device__ SkfStage(const GemmParamsT<float>& p_, float* ws_, int pk_, int piece) : p(p_), ws(ws_), pk(pk_) {
-    kbeg = piece * p.sub_len;
-    kend = min(kbeg + p.sub_len, p.K);
-    spare = 16 * ((p.N + 15) >> 4) * pk;
-    ldb = (int)p.ldb;
-    rb = sk_rsrc(p.B + kbeg);
-  }
-  __device__ int rounds(int c0, int c1) const {
-    const int total = p.N * (c1 - c0);
-    return total > 0 ? (total + SKF_BATCH * SKF_NT - 1) / (SKF_BATCH * SKF_NT) : 0;
-  }
-  // round q of the part's loads
-  __device__ void issue(SkfChunks& g, int c0, int c1, int q) const {
-    const int w = c1 - c0, total = p.N * w;
-    const unsigned mq = w > 0 ? 0xffffffffu / (unsigned)w + 1u : 0u;
-#pragma unroll
-    for (int j = 0; j < SKF_BATCH; ++j) {
-      const int i = (q * SKF_BATCH + j) * SKF_NT + (int)threadIdx.x;
-      const int u = (int)__umulhi((unsigned)i, mq), c = c0 + i - u * w;
-      const bool in = i < total;
-      g.at[j] = in ? u * pk + 4 * c : spare;
-      g.v[j] = sk_load(rb, in && kbeg + 4 * c < kend ? 4u * (unsigned)(u * ldb + 4 * c) : SK_OOB);
-    }
-  }
-  __device__ void store(const SkfChunks& g) const {
-#pragma unroll
-    for (int j = 0; j < SKF_BATCH; ++j) *reinterpret_cast<floatx4*>(ws + g.at[j]) = g.v[j];
-  }
-  // rounds from q0 on, each loaded and stored in turn
-  __device__ void copy(int c0, int c1, int q0) const {
-    const int nq = rounds(c0, c1);
-    for (int q = q0; q < nq; ++q) {
-      SkfChunks g;
-      issue(g, c0, c1, q);
-      store(g);
-    }
-  }
-};
-
-__global__ void __launch_bounds__(SKF_NT) fwd_skinny_kernel(const GemmParamsT<float> p, int pk) {
-  extern __shared__ floatx4 ws4[];
-  float* ws = reinterpret_cast<float*>(ws4);
-  // workgroup b: piece b % nsub, sample blocks 8 (b / nsub) .. + 7
-  const int piece = blockIdx.x % p.nsub;
-  const int sblk = 8 * (blockIdx.x / p.nsub) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  SkfStage stage(p, ws, pk, piece);
+template <int WU>
+__global__ void __launch_bounds__(SKF_NT) fwd_skinny_kernel(const GemmParamsT<float> p, int slice) {
+  extern __shared__ uintx4 ws4[];
+  char* ws = reinterpret_cast<char*>(ws4);
+  // workgroup b: piece b % nsub, sample blocks of group b / nsub
+  const int piece = blockIdx.x % p.nsub, group = blockIdx.x / p.nsub;
   switch ((p.N + 15) >> 4) {
-    case 1: fwd_skinny_tile<1>(p, sblk, piece, ws, pk, stage); break;
-    case 2: fwd_skinny_tile<2>(p, sblk, piece, ws, pk, stage); break;
-    case 3: fwd_skinny_tile<3>(p, sblk, piece, ws, pk, stage); break;
-    case 4: fwd_skinny_tile<4>(p, sblk, piece, ws, pk, stage); break;
-    case 5: fwd_skinny_tile<5>(p, sblk, piece, ws, pk, stage); break;
-    case 6: fwd_skinny_tile<6>(p, sblk, piece, ws, pk, stage); break;
-    case 7: fwd_skinny_tile<7>(p, sblk, piece, ws, pk, stage); break;
-    default: fwd_skinny_tile<8>(p, sblk, piece, ws, pk, stage); break;
+    case 1: fwd_skinny_tile<1, WU>(p, group, piece, ws, slice); break;
+    case 2: fwd_skinny_tile<2, WU>(p, group, piece, ws, slice); break;
+    case 3: fwd_skinny_tile<3, WU>(p, group, piece, ws, slice); break;
+    case 4: fwd_skinny_tile<4, WU>(p, group, piece, ws, slice); break;
+    case 5: fwd_skinny_tile<5, WU>(p, group, piece, ws, slice); break;
+    case 6: fwd_skinny_tile<6, WU>(p, group, piece, ws, slice); break;
+    case 7: fwd_skinny_tile<7, WU>(p, group, piece, ws, slice); break;
+    default: fwd_skinny_tile<8, WU>(p, group, piece, ws, slice); break;
   }
 }
+
+// bytes of LDS of one k-group of every part
+int skf_group_bytes(int N) { return 3 * 4 * (16 * ((N + 15) / 16) * 16 + 32); }
 
 }  // namespace
 
@@ -703,12 +806,12 @@ hipError_t launch_dw_skinny_group(SkinnyGroup g, hipStream_t s) {
     if (p.M <= 0 || p.M > SKINNY_MAX_UNITS || p.N <= 0 || p.K < 0 || g.npieces[q] <= 0)
       return hipErrorInvalidValue;
     if (p.nsub <= 0 || g.npieces[q] % p.nsub != 0) return hipErrorInvalidValue;
-    // 16-byte loads of rows and stores of tendency rows: pitches of whole
-    // vectors, 16-byte aligned bases
-    if (p.lda % 4 != 0 || p.ldb % 4 != 0 || p.ld0 % 4 != 0 || p.pstride % 4 != 0 ||
-        p.lda < 4 * ((p.M + 3) / 4) || p.ldb < 4 * ((p.N + 3) / 4) || p.ld0 < 4 * ((p.N + 3) / 4))
+    // 16-byte loads of delta rows and stores of tendency rows: pitches of
+    // whole vectors, 16-byte aligned bases; input rows of any pitch
+    if (p.lda % 4 != 0 || p.ld0 % 4 != 0 || p.pstride % 4 != 0 || p.lda < 4 * ((p.M + 3) / 4) ||
+        p.ldb < p.N || p.ld0 < 4 * ((p.N + 3) / 4))
       return hipErrorInvalidValue;
-    if ((reinterpret_cast<uintptr_t>(p.A) & 15) != 0 || (reinterpret_cast<uintptr_t>(p.B) & 15) != 0 ||
+    if ((reinterpret_cast<uintptr_t>(p.A) & 15) != 0 || (reinterpret_cast<uintptr_t>(p.B) & 3) != 0 ||
         (reinterpret_cast<uintptr_t>(p.partial) & 15) != 0)
       return hipErrorInvalidValue;
     // a k-step's offsets are 32-bit, within 4 rows of its first row
@@ -720,19 +823,6 @@ hipError_t launch_dw_skinny_group(SkinnyGroup g, hipStream_t s) {
   for (int q = g.n + 1; q <= GEMM_GROUP_MAX; ++q) g.start[q] = g.start[g.n];
   if (g.start[g.n] <= 0) return hipErrorInvalidValue;
   return launch_k(skinny_dw_kernel, dim3((unsigned)g.start[g.n]), dim3(SK_NT), 0, s, g);
-}
-
-int fwd_skinny_pitch(int sub_len) {
-  // whole k-groups, then a multiple of 4 floats whose quarter is odd: rows
-  // r = 0..15 of a 16-byte fragment read start in 16 distinct groups of 4
-  // banks
-  const int q = 4 * ((sub_len + 15) / 16);
-  return 4 * (q % 2 == 1 ? q : q + 1);
-}
-
-int64_t fwd_skinny_lds_bytes(int N, int sub_len) {
-  // the slice's rows, padded to 16 units, and a spare 16-byte slot
-  return (int64_t)16 * ((N + 15) / 16) * fwd_skinny_pitch(sub_len) * 4 + 16;
 }
 
 hipError_t launch_dw_skinny_group64(SkinnyGroup64 g, hipStream_t s) {
@@ -759,24 +849,26 @@ hipError_t launch_dw_skinny_group64(SkinnyGroup64 g, hipStream_t s) {
   return launch_k(skinny_dw64_kernel, dim3((unsigned)g.start[g.n]), dim3(SK_NT), 0, s, g);
 }
 
-hipError_t launch_fwd_skinny(const GemmParamsT<float>& p, hipStream_t s) {
+hipError_t launch_fwd_skinny(const GemmParamsT<float>& p, int rows, hipStream_t s) {
+  if (rows != 128 && rows != 32) return hipErrorInvalidValue;
   if (p.M <= 0 || p.N <= 0 || p.N > SKINNY_MAX_UNITS || p.K <= 0 || p.nsub <= 0)
     return hipErrorInvalidValue;
   // pieces after the first start on whole k-groups; 16-byte row loads
   if (p.sub_len <= 0 || (p.nsub > 1 && p.sub_len % 16 != 0) || (int64_t)p.nsub * p.sub_len < p.K ||
       (int64_t)(p.nsub - 1) * p.sub_len >= p.K)
     return hipErrorInvalidValue;
-  if (p.K % 4 != 0 || p.lda % 4 != 0 || p.ldb % 4 != 0 || p.lda < p.K || p.ldb < p.K ||
-      p.ld0 < p.N)
-    return hipErrorInvalidValue;
-  if ((reinterpret_cast<uintptr_t>(p.A) & 15) != 0 || (reinterpret_cast<uintptr_t>(p.B) & 15) != 0)
+  if (p.ldb % 4 != 0 || p.lda < p.K || p.ldb < p.K || p.ld0 < p.N) return hipErrorInvalidValue;
+  if ((reinterpret_cast<uintptr_t>(p.A) & 3) != 0 || (reinterpret_cast<uintptr_t>(p.B) & 15) != 0)
     return hipErrorInvalidValue;
   // 32-bit offsets: 16 rows of A past the block's first row, every row of B
   if ((int64_t)16 * p.lda * 4 >= (int64_t)SK_OOB || (int64_t)p.N * p.ldb * 4 >= (int64_t)SK_OOB)
     return hipErrorInvalidValue;
-  const int64_t lds = fwd_skinny_lds_bytes(p.N, p.sub_len);
-  if (lds > SKINNY_FWD_LDS) return hipErrorInvalidValue;
-  const int64_t groups = ((int64_t)p.M + 127) / 128;
+  // the piece's k-groups in the fewest slices that fit, of equal length
+  const int len = p.sub_len < p.K ? p.sub_len : p.K, groups32 = (len + 31) / 32;
+  const int most = SKINNY_FWD_LDS / skf_group_bytes(p.N);
+  const int slices = (groups32 + most - 1) / most, slice = (groups32 + slices - 1) / slices;
+  const int lds = slice * skf_group_bytes(p.N);
+  const int64_t groups = ((int64_t)p.M + rows - 1) / rows;
   if (groups * p.nsub > 0x7fffffff) return hipErrorInvalidValue;
   // the kernel may use more than the default dynamic LDS: allowed once per
   // device (any thread may get there first; the call is idempotent)
@@ -786,13 +878,15 @@ hipError_t launch_fwd_skinny(const GemmParamsT<float>& p, hipStream_t s) {
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= kDevices || !attr_set[dev].load(std::memory_order_acquire)) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(fwd_skinny_kernel),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, SKINNY_FWD_LDS);
-    if (e != hipSuccess) return e;
+    for (const void* k : {reinterpret_cast<const void*>(fwd_skinny_kernel<1>),
+                          reinterpret_cast<const void*>(fwd_skinny_kernel<4>)}) {
+      e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, SKINNY_FWD_LDS);
+      if (e != hipSuccess) return e;
+    }
     if (dev >= 0 && dev < kDevices) attr_set[dev].store(true, std::memory_order_release);
   }
-  return launch_k(fwd_skinny_kernel, dim3((unsigned)(groups * p.nsub)), dim3(SKF_NT),
-                  (unsigned)lds, s, p, fwd_skinny_pitch(p.sub_len));
+  return launch_k(rows == 128 ? fwd_skinny_kernel<1> : fwd_skinny_kernel<4>,
+                  dim3((unsigned)(groups * p.nsub)), dim3(SKF_NT), (unsigned)lds, s, p, slice);
 }
 
 }  // namespace nf

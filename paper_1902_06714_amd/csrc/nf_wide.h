@@ -2,11 +2,8 @@
 // output and hidden deltas, tendencies; sections 3.2 - 3.5), on the bf16
 // matrix cores.
 //
-// An fp32 value x is the sum of three bf16 values to its last bit: h = bf16(x),
-// m = bf16(x - h), l = bf16(x - h - m), each rounded to nearest, so |m| <= 2^-9
-// |x| and |l| <= 2^-18 |x|.  A product a b is then formed as the six products
-// hh, hm, mh, mm, hl, lh (each exact: 8 x 8 significand bits), accumulated in
-// fp32; what is left out (ml, lm, ll) is below 2^-25 |a b|.
+// Every operand is split into three bf16 parts and a product formed as six
+// (nf_parts.h).
 //
 // Why: the fp32 matrix instruction gives 64 flops a clock and SIMD, the bf16
 // one 1024, so six of them are worth 171, 2.7 times as many.  The sums are
@@ -34,34 +31,12 @@
 
 #include "nf_act.h"
 #include "nf_internal.h"
+#include "nf_parts.h"
 #include "nf_split.h"
 
 namespace nf {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
-typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
-
 constexpr int WIDE_KI = 16;      // k of one 32x32x16 matrix instruction
-
-__device__ __forceinline__ unsigned pack_bf16(float a, float b) {
-  const floatx2 f = {a, b};
-  return __builtin_bit_cast(unsigned, __builtin_convertvector(f, bf16x2));
-}
-
-// The three bf16 parts of two values, packed (a in the low half).
-__device__ __forceinline__ void split3(float a, float b, unsigned& h, unsigned& m, unsigned& l) {
-  h = pack_bf16(a, b);
-  const float a1 = a - __builtin_bit_cast(float, h << 16);
-  const float b1 = b - __builtin_bit_cast(float, h & 0xffff0000u);
-  m = pack_bf16(a1, b1);
-  l = pack_bf16(a1 - __builtin_bit_cast(float, m << 16),
-                b1 - __builtin_bit_cast(float, m & 0xffff0000u));
-}
 
 // bytes of LDS: nb stages, and a flag
 constexpr int wide_lds(int BM, int BN, int BK, int nb) {
@@ -379,12 +354,7 @@ __device__ __forceinline__ void clear(floatx16 (&acc)[TM][TN]) {
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 }
 
-// Whether the sums of the six products cannot be trusted.  An operand that is
-// not finite, or that rounds to infinity in bf16, leaves a NaN or an infinity
-// in every sum it enters; operands so small that their last parts are below
-// the smallest normal number, which the matrix cores read as zeros, leave a
-// tiny sum.  Such a tile is done again on the fp32 matrix cores.
-constexpr float WIDE_TINY = 8.271806e-25f;   // 2^-80
+// Whether any of the sums cannot be trusted.
 template <int TM, int TN>
 __device__ __forceinline__ bool doubtful(const floatx16 (&acc)[TM][TN]) {
   bool bad = false;
@@ -393,10 +363,7 @@ __device__ __forceinline__ bool doubtful(const floatx16 (&acc)[TM][TN]) {
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const float c = fabsf(acc[i][j][v]);
-        bad |= !(c < __builtin_inff()) || (c > 0.f && c < WIDE_TINY);
-      }
+      for (int v = 0; v < 16; ++v) bad |= parts_doubtful(acc[i][j][v]);
   return bad;
 }
 
@@ -442,8 +409,6 @@ __device__ __forceinline__ void put_bias_sums(const GemmParamsT<float>& p, const
   }
 }
 
-// The six products of one pair of operand fragments, the small ones first.
-constexpr int WIDE_PA[6] = {2, 0, 1, 1, 0, 0}, WIDE_PB[6] = {0, 2, 1, 0, 1, 0};
 #define NF_MMA(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0)
 
 // One BM x BN tile by (BM / WM) x (BN / WN) waves of WM x WN that all load and
@@ -522,7 +487,7 @@ __device__ __forceinline__ void wide_tile(const GemmParamsT<float>& p, int bx, i
         for (int i = 0; i < TM; ++i)
 #pragma unroll
           for (int j = 0; j < TN; ++j)
-            acc[i][j] = NF_MMA(a[cur][i][WIDE_PA[x]], b[cur][j][WIDE_PB[x]], acc[i][j]);
+            acc[i][j] = NF_MMA(a[cur][i][PART_A[x]], b[cur][j][PART_B[x]], acc[i][j]);
       deliver(cur, lds + cur * STAGE);
       request(cur, t + 4);
 #pragma unroll
@@ -542,7 +507,7 @@ __device__ __forceinline__ void wide_tile(const GemmParamsT<float>& p, int bx, i
         for (int x = 0; x < 6; ++x)
 #pragma unroll
           for (int j = 0; j < TN; ++j)
-            acc[i][j] = NF_MMA(a[0][i][WIDE_PA[x]], b[0][j][WIDE_PB[x]], acc[i][j]);
+            acc[i][j] = NF_MMA(a[0][i][PART_A[x]], b[0][j][PART_B[x]], acc[i][j]);
       }
       deliver(cur ^ 1, lds + (cur ^ 1) * STAGE);
       request(cur ^ 1, t + 3);
@@ -710,7 +675,7 @@ __device__ __forceinline__ void wide_tile_roles(const GemmParamsT<float>& p, int
 #pragma unroll
           for (int j = 0; j < TN; ++j) {
             floatx16& c = x == 5 ? acc[i][j] : small[i][j];
-            c = NF_MMA(a[u & 1][i][WIDE_PA[x]], b[u & 1][j][WIDE_PB[x]], c);
+            c = NF_MMA(a[u & 1][i][PART_A[x]], b[u & 1][j][PART_B[x]], c);
           }
       __syncthreads();
     }

@@ -1,0 +1,66 @@
+"""Input rows that are not whole 16-byte vectors: odd widths and rows that
+start off a 16-byte boundary, through the skinny forward
+and tendency kernels and the medium inference.  The last row ends at the end of
+the tensor, and no value of a row may reach its neighbour."""
+
+import numpy as np
+import pytest
+
+from oracle import mlp
+
+from . import parity
+from .gpu_run import GpuNet, note, to_dev
+from .test_gpu_parity import _compare_trajectory, _problem
+
+pytestmark = pytest.mark.gpu
+
+# dims, acts, batch, shards, kernels of the training step, of inference
+CASES = [
+    ((33, 40, 10), ("tanh", "sigmoid"), 1, 1, ("fwd_skinny",), "medium_infer"),
+    ((129, 77, 33, 5), ("gaussian", "tanh", "sigmoid"), 2049, 1, ("fwd_skinny", "dw_skinny"), "medium_infer"),
+    ((785, 100, 100, 10), ("tanh", "tanh", "sigmoid"), 1600, 16, ("fwd_skinny", "dw_skinny"), "medium_infer"),
+    ((111, 128, 16, 7, 3), ("tanh",), 1000, 4, ("fwd_skinny", "dw_skinny"), "medium_infer"),
+    ((2050, 113, 9), ("tanh", "sigmoid"), 515, 5, ("fwd_skinny", "dw_skinny"), "medium_infer"),
+    ((784, 100, 30), ("sigmoid",), 6001, 1, ("fwd_skinny", "dw_skinny"), "medium_infer"),
+]
+
+
+@pytest.mark.parametrize("dims,acts,batch,shards,train,infer", CASES)
+def test_odd_rows(dims, acts, batch, shards, train, infer):
+    theta, X, Y = _problem(dims, 13 * sum(dims) + batch, 2 * batch)
+    _compare_trajectory(dims, acts, theta, X, Y, batch, 0.3, shards, 2)
+    ref = mlp.output(theta.astype(np.float64), dims, parity.full_acts(dims, acts), X[:batch])
+    with GpuNet(dims, acts, theta) as net:
+        net.nf.nf_profile(net.h, 1)
+        out = net.forward(to_dev(X[:batch]))
+        ran = {k["name"] for k in net.nf.nf_profile_read(net.h)}
+        # the same rows from an address that is 4 bytes past a 16-byte boundary
+        flat = to_dev(np.concatenate([[0.0], X[:batch].ravel()]))
+        off = net.forward(flat[1:].view(batch, dims[0]))
+        net.nf.nf_profile_read(net.h)
+        net.train_batch(to_dev(X[:batch]), to_dev(Y[:batch]), 0.3, shards)
+        trained = {k["name"] for k in net.nf.nf_profile_read(net.h)}
+        net.nf.nf_profile(net.h, 0)
+    # an fp32 sum of at most 2050 products of values below 1, through at most
+    # four layers of slope at most 1
+    assert np.max(np.abs(out - ref)) < 2e-5
+    assert np.max(np.abs(off - ref)) < 2e-5
+    assert infer in ran, ran
+    assert all(k in trained for k in train), trained
+
+
+@pytest.mark.parametrize("dims,batch", [((129, 77, 33, 5), 40),
+                                        ((785, 100, 10), 130)])
+def test_rows_do_not_leak(dims, batch):
+    """A row of NaN leaves the rows before and after it as they were."""
+    theta, X, _ = _problem(dims, 7 * sum(dims), batch)
+    with GpuNet(dims, ("sigmoid",), theta) as net:
+        clean = net.forward(to_dev(X))
+        bad = np.arange(1, batch, 5)
+        X[bad] = np.nan
+        out = net.forward(to_dev(X))
+    note(f"row leak dims={dims} batch={batch}")
+    rest = np.setdiff1d(np.arange(batch), bad)
+    assert np.isnan(out[bad]).all()
+    # (rows that share a block with a NaN are formed on the fp32 matrix cores)
+    assert np.max(np.abs(out[rest] - clean[rest])) < 2e-5
