@@ -260,7 +260,8 @@ inline int64_t narrow_pack_w1f_elems(int d0) { return (int64_t)((d0 + 63) / 64) 
 inline int64_t narrow_pack_w1i_elems(int d0) { return (int64_t)((d0 + 15) / 16) * NARROW_PACK_W1I_BLOCK; }
 template <class T>
 struct NarrowFwdParamsT {
-  const T* X;                              // [B][d0], d0 % (16 / sizeof(T)) == 0, 16-byte aligned
+  const T* X;                              // [B][d0]; fp32: d0 >= 4 or a multiple of 4; fp64:
+                                           // d0 even, 16-byte aligned
   const T* Y;                              // [B][d_L] targets (training)
   int B, d0, L;
   int dout;                                // d_L

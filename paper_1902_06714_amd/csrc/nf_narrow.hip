@@ -47,6 +47,17 @@ __device__ __forceinline__ float4 lane_permute4(int src_byte, float4 v) {
   return o;
 }
 
+// Input rows of a width that is not a multiple of 4, or at an address that is
+// not a multiple of 16 (ODD): a row's last vector is read at its last whole
+// one (width - 4, inside the row) and its values moved down, with zeros
+// behind them, so no load leaves the row.  The hardware takes 16-byte loads at
+// any 4-byte address.
+__device__ __forceinline__ float4 move_down(float4 v, int by) {
+  const bool one = by & 1, two = by & 2;
+  const float4 a = make_float4(one ? v.y : v.x, one ? v.z : v.y, one ? v.w : v.z, one ? 0.0f : v.w);
+  return make_float4(two ? a.z : a.x, two ? a.w : a.y, two ? 0.0f : a.z, two ? 0.0f : a.w);
+}
+
 // A buffer offset past every range the narrow kernels read through buffer
 // resources: a load there returns zeros without touching memory.
 constexpr unsigned NB_OOB = NARROW_OOB;
@@ -247,7 +258,7 @@ __device__ __forceinline__ void narrow_tail(const NarrowFwdParams& p, int s0, in
 // 16-sample tiles (large batches): layer 1 on the 16x16x4 matrix cores, the
 // input width staged through LDS in 128-wide chunks.
 // ---------------------------------------------------------------------------
-template <bool TRAIN, int N1_PRE>
+template <bool TRAIN, int N1_PRE, bool ODD>
 __global__ void __launch_bounds__(N1_WAVES * 64) narrow_fwd16_kernel(const NarrowFwdParams p) {
   constexpr int T = NARROW_TILE;
   constexpr int NW = NARROW_WIDTH;
@@ -303,7 +314,15 @@ __global__ void __launch_bounds__(N1_WAVES * 64) narrow_fwd16_kernel(const Narro
         const int k = (cb + u) * N1_KC + 4 * xq;
         const bool k_ok = k < p.d0;
         const int kc = k_ok ? k : 0;
-        const float4 xv = *reinterpret_cast<const float4*>(xsrc + kc);
+        float4 xv;
+        if constexpr (ODD) {
+          typedef float unaligned4 __attribute__((ext_vector_type(4), aligned(4)));
+          const int at = kc < p.d0 - 4 ? kc : p.d0 - 4;
+          const unaligned4 q = *reinterpret_cast<const unaligned4*>(xsrc + at);
+          xv = move_down(make_float4(q[0], q[1], q[2], q[3]), kc - at);
+        } else {
+          xv = *reinterpret_cast<const float4*>(xsrc + kc);
+        }
         const float4 w0 = *reinterpret_cast<const float4*>(wsrc0 + kc);
         const float4 w1 = *reinterpret_cast<const float4*>(wsrc1 + kc);
         xr[u] = keep_if(k_ok && xrow_ok, xv);
@@ -378,7 +397,7 @@ constexpr int N4_RP = 36;                    // padded row: conflict-free stores
 constexpr int N4_SS = N4_PARTS * N4_RP + 32; // sample stride (other bank half)
 static_assert(N1_WAVES * 64 == 4 * N4_T * NARROW_WIDTH, "four partial sums per output");
 
-template <bool TRAIN>
+template <bool TRAIN, bool ODD>
 __global__ void __launch_bounds__(N1_WAVES * 64) narrow_fwd4_kernel(const NarrowFwdParams p) {
   constexpr int T = N4_T;
   constexpr int NW = NARROW_WIDTH;
@@ -428,8 +447,9 @@ __global__ void __launch_bounds__(N1_WAVES * 64) narrow_fwd4_kernel(const Narrow
     int t0 = wave;
     do {
       // all loads of the block first; inputs past the width load as zeros
-      // (the width is a multiple of 4, so a float4 is wholly in or out)
+      // (a float4 is wholly in or out, or with ODD moved into the row)
       float4 xr[N4_PRE], wr[N4_PRE][N4_UG];
+      int shift[N4_PRE];
 #pragma unroll
       for (int u = 0; u < N4_PRE; ++u) {
         int t = t0 + u * N1_WAVES;
@@ -437,8 +457,10 @@ __global__ void __launch_bounds__(N1_WAVES * 64) narrow_fwd4_kernel(const Narrow
         if (tin) t = t + rot < nsteps ? t + rot : t + rot - nsteps;
         const int kx = t * N4_KS + 4 * bx;
         const bool okx = tin && kx < p.d0;
+        const int ax = ODD && kx > p.d0 - 4 ? p.d0 - 4 : kx;
         xr[u] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(
-                                               xres, okx ? 4 * (qx * p.d0 + kx) : (int)NB_OOB, 0, 0));
+                                               xres, okx ? 4 * (qx * p.d0 + ax) : (int)NB_OOB, 0, 0));
+        shift[u] = kx - ax;
 #pragma unroll
         for (int ug = 0; ug < N4_UG; ++ug)
           wr[u][ug] = __builtin_bit_cast(
@@ -448,7 +470,10 @@ __global__ void __launch_bounds__(N1_WAVES * 64) narrow_fwd4_kernel(const Narrow
       // keep every load of the block ahead of the first matrix instruction
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int u = 0; u < N4_PRE; ++u) xr[u] = lane_permute4(src_byte, xr[u]);
+      for (int u = 0; u < N4_PRE; ++u) {
+        if constexpr (ODD) xr[u] = move_down(xr[u], shift[u]);
+        xr[u] = lane_permute4(src_byte, xr[u]);
+      }
 #pragma unroll
       for (int u = 0; u < N4_PRE; ++u) {
 #pragma unroll
@@ -961,9 +986,14 @@ int narrow_infer_grid(const NarrowFwdParams& p) {
   return ntiles < p.ncu ? ntiles : p.ncu;
 }
 
+// whether input rows need the ODD kernels
+bool narrow_odd_rows(const NarrowFwdParams& p) {
+  return p.d0 % 4 != 0 || (reinterpret_cast<uintptr_t>(p.X) & 15) != 0;
+}
+
 NarrowKernel narrow_fwd_kernel(bool train, const NarrowFwdParams& p) {
   if (p.B <= NARROW_SMALL_BATCH) return NK_FWD4;
-  if (!train && p.ncu > 0 && p.d0 <= NI_MW * NI_MC_MAX * NI_CH) {
+  if (!train && !narrow_odd_rows(p) && p.ncu > 0 && p.d0 <= NI_MW * NI_MC_MAX * NI_CH) {
     const int64_t ntiles = (p.B + NARROW_TILE - 1) / NARROW_TILE;
     const int64_t grid = narrow_infer_grid(p);
     const int64_t rows = (ntiles + grid - 1) / grid * NARROW_TILE;
@@ -974,20 +1004,24 @@ NarrowKernel narrow_fwd_kernel(bool train, const NarrowFwdParams& p) {
 
 hipError_t launch_narrow_fwd(bool train, const NarrowFwdParams& p, hipStream_t s) {
   const dim3 block(N1_WAVES * 64);
+  const bool odd = narrow_odd_rows(p);
+  if (odd && (p.d0 < 4 || (reinterpret_cast<uintptr_t>(p.X) & 3) != 0)) return hipErrorInvalidValue;
   switch (narrow_fwd_kernel(train, p)) {
     case NK_FWD4: {
       const dim3 grid((p.B + N4_T - 1) / N4_T);
-      if (train)
-        return launch_k(narrow_fwd4_kernel<true>, grid, block, 0, s, p);
-      else
-        return launch_k(narrow_fwd4_kernel<false>, grid, block, 0, s, p);
+      if (odd)
+        return train ? launch_k(narrow_fwd4_kernel<true, true>, grid, block, 0, s, p)
+                     : launch_k(narrow_fwd4_kernel<false, true>, grid, block, 0, s, p);
+      return train ? launch_k(narrow_fwd4_kernel<true, false>, grid, block, 0, s, p)
+                   : launch_k(narrow_fwd4_kernel<false, false>, grid, block, 0, s, p);
     }
     case NK_FWD16: {
       const dim3 grid((p.B + NARROW_TILE - 1) / NARROW_TILE);
-      if (train)
-        return launch_k(narrow_fwd16_kernel<true, N1_PRE_TRAIN>, grid, block, 0, s, p);
-      else
-        return launch_k(narrow_fwd16_kernel<false, N1_PRE_INFER>, grid, block, 0, s, p);
+      if (odd)
+        return train ? launch_k(narrow_fwd16_kernel<true, N1_PRE_TRAIN, true>, grid, block, 0, s, p)
+                     : launch_k(narrow_fwd16_kernel<false, N1_PRE_INFER, true>, grid, block, 0, s, p);
+      return train ? launch_k(narrow_fwd16_kernel<true, N1_PRE_TRAIN, false>, grid, block, 0, s, p)
+                   : launch_k(narrow_fwd16_kernel<false, N1_PRE_INFER, false>, grid, block, 0, s, p);
     }
     case NK_INFER: {
       const dim3 grid(narrow_infer_grid(p));

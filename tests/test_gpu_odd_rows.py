@@ -1,5 +1,5 @@
 """Input rows that are not whole 16-byte vectors: odd widths and rows that
-start off a 16-byte boundary, through the skinny forward
+start off a 16-byte boundary, through the narrow kernels, the skinny forward
 and tendency kernels and the medium inference.  The last row ends at the end of
 the tensor, and no value of a row may reach its neighbour."""
 
@@ -16,6 +16,12 @@ pytestmark = pytest.mark.gpu
 
 # dims, acts, batch, shards, kernels of the training step, of inference
 CASES = [
+    ((5, 3), ("sigmoid",), 7, 1, ("narrow_fwd4_train",), "narrow_fwd4_infer"),
+    ((61, 17, 2), ("tanh", "sigmoid"), 33, 1, ("narrow_fwd4_train",), "narrow_fwd4_infer"),
+    ((65, 32, 31, 4), ("gaussian", "tanh", "sigmoid"), 129, 1, ("narrow_fwd4_train",), "narrow_fwd4_infer"),
+    ((785, 30, 10), ("sigmoid",), 1000, 1, ("narrow_fwd4_train",), "narrow_fwd4_infer"),
+    ((1027, 12, 10), ("tanh", "sigmoid"), 2049, 1, ("narrow_fwd16_train",), "narrow_fwd16_infer"),
+    ((7, 32, 32, 32, 32), ("sigmoid",), 2065, 1, ("narrow_fwd16_train",), "narrow_fwd16_infer"),
     ((33, 40, 10), ("tanh", "sigmoid"), 1, 1, ("fwd_skinny",), "medium_infer"),
     ((129, 77, 33, 5), ("gaussian", "tanh", "sigmoid"), 2049, 1, ("fwd_skinny", "dw_skinny"), "medium_infer"),
     ((785, 100, 100, 10), ("tanh", "tanh", "sigmoid"), 1600, 16, ("fwd_skinny", "dw_skinny"), "medium_infer"),
@@ -49,7 +55,7 @@ def test_odd_rows(dims, acts, batch, shards, train, infer):
     assert all(k in trained for k in train), trained
 
 
-@pytest.mark.parametrize("dims,batch", [((129, 77, 33, 5), 40),
+@pytest.mark.parametrize("dims,batch", [((61, 17, 2), 33), ((1027, 12, 10), 2049), ((129, 77, 33, 5), 40),
                                         ((785, 100, 10), 130)])
 def test_rows_do_not_leak(dims, batch):
     """A row of NaN leaves the rows before and after it as they were."""
