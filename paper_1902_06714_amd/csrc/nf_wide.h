@@ -438,8 +438,13 @@ __device__ __forceinline__ void wide_tile(const GemmParamsT<float>& p, int bx, i
   const int ntiles = kend > kbeg ? (kend - kbeg + BK - 1) / BK : 0;
   constexpr bool DW = EPI == EPI_DW_SGD || EPI == EPI_DW_PARTIAL;
 
-  floatx16 acc[TM][TN];
+  // the hh products and the five small ones in accumulators of their own, where
+  // the registers hold both (not in the 256 x 256 tile): the sum of hh is
+  // rounded once for 16 k, not six times
+  constexpr bool APART = TM * TN <= 4;
+  floatx16 acc[TM][TN], small[APART ? TM : 1][APART ? TN : 1];
   clear(acc);
+  clear(small);
   float bsum[LA::Q] = {};
   LA la[2];
   LB lb[2];
@@ -486,8 +491,10 @@ __device__ __forceinline__ void wide_tile(const GemmParamsT<float>& p, int bx, i
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int j = 0; j < TN; ++j)
-            acc[i][j] = NF_MMA(a[cur][i][PART_A[x]], b[cur][j][PART_B[x]], acc[i][j]);
+          for (int j = 0; j < TN; ++j) {
+            floatx16& c = x == 5 || !APART ? acc[i][j] : small[APART ? i : 0][APART ? j : 0];
+            c = NF_MMA(a[cur][i][PART_A[x]], b[cur][j][PART_B[x]], c);
+          }
       deliver(cur, lds + cur * STAGE);
       request(cur, t + 4);
 #pragma unroll
@@ -506,8 +513,10 @@ __device__ __forceinline__ void wide_tile(const GemmParamsT<float>& p, int bx, i
 #pragma unroll
         for (int x = 0; x < 6; ++x)
 #pragma unroll
-          for (int j = 0; j < TN; ++j)
-            acc[i][j] = NF_MMA(a[0][i][PART_A[x]], b[0][j][PART_B[x]], acc[i][j]);
+          for (int j = 0; j < TN; ++j) {
+            floatx16& c = x == 5 || !APART ? acc[i][j] : small[APART ? i : 0][APART ? j : 0];
+            c = NF_MMA(a[0][i][PART_A[x]], b[0][j][PART_B[x]], c);
+          }
       }
       deliver(cur ^ 1, lds + (cur ^ 1) * STAGE);
       request(cur ^ 1, t + 3);
@@ -542,6 +551,12 @@ __device__ __forceinline__ void wide_tile(const GemmParamsT<float>& p, int bx, i
     stage(1, t + 1);
   }
 
+  if constexpr (APART) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] += small[i][j];
+  }
   if (__syncthreads_or(doubtful(acc))) {
     float* const as = reinterpret_cast<float*>(lds);
     float* const bs = as + BK * BM;
