@@ -307,7 +307,8 @@ int pick_tile(int64_t M, int64_t N, int64_t splits) {
 // 39 and 106), the 128 x 128 tile from about one per CU (4096x1024x1024: 48.5
 // against 63 and 107), the 256 x 256 tile where its own grid fills the chip.
 // (The 128 x 128 tile's figures are from its form with one set of accumulators;
-// the present one takes 4 to 8% longer in whole passes of 784-1024^3-10.)
+// the present one takes 8% longer in inference of 784-1024^3-10 and 20% in its
+// tendencies, 152 us then and 182 now, the same in its forward and deltas.)
 int64_t wide_tiles(int tile, int64_t M, int64_t N) {
   const int64_t side = tile == nf::TILE_256x256 ? 256 : (tile == nf::TILE_128x128 ? 128 : 64);
   return ((M + side - 1) / side) * ((N + side - 1) / side);
