@@ -1,10 +1,19 @@
-// An fp32 value as three bf16 values, for products on the bf16 matrix cores.
+// An fp32 value as three bf16 values, for products on the bf16 matrix cores
+// (the splitting of Henry, Tang and Heinecke, "Leveraging the bfloat16
+// Artificial Intelligence Datatype For Higher-Precision Computations",
+// arXiv:1904.06376).
 //
-// x = h + m + l to its last bit, h = bf16(x), m = bf16(x - h), l = bf16(x - h -
-// m), each rounded to nearest, so |m| <= 2^-9 |x| and |l| <= 2^-18 |x|.  A
-// product a b is formed as the six products hh, hm, mh, mm, hl, lh, each exact
-// (8 x 8 significand bits), accumulated in fp32; what is left out (ml, lm,
-// ll) is below 2^-25 |a b|.
+// 2^23 x = h + m + l to its last bit, h = bf16(2^23 x), m = bf16(2^23 x - h), l =
+// bf16(2^23 x - h - m), each rounded to nearest, so |m| <= 2^-9 |h| and |l| <=
+// 2^-18 |h|.  A product a b is formed as the six products hh, hm, mh, mm, hl,
+// lh, each exact (8 x 8 significand bits), accumulated in fp32, and the sum is
+// multiplied by 2^-46; what is left out (ml, lm, ll) is below 2^-25 |a b|.
+//
+// Why 2^23: the matrix cores read subnormal bf16 values as zeros.  Every fp32
+// value is a multiple of 2^-149, so are its unscaled parts, and those below
+// 2^-126 would be lost: 1e-36 times 1e13 came out 8e-4 off, 1e-39 times 1e30 as
+// zero.  Scaled, a part that is not zero is at least 2^-126.  It costs a
+// multiplication per value split (13 vector instructions for two, not 11).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -24,8 +33,12 @@ __device__ __forceinline__ unsigned pack_bf16(float a, float b) {
   return __builtin_bit_cast(unsigned, __builtin_convertvector(f, bf16x2));
 }
 
-// The three bf16 parts of two values, packed (a in the low half).
+// The three bf16 parts of two values times PARTS_SCALE, packed (a in the low half).
+constexpr float PARTS_SCALE = 8388608.f;                       // 2^23
+constexpr float PARTS_UNSCALE = 1.f / PARTS_SCALE / PARTS_SCALE;
 __device__ __forceinline__ void split3(float a, float b, unsigned& h, unsigned& m, unsigned& l) {
+  a *= PARTS_SCALE;
+  b *= PARTS_SCALE;
   h = pack_bf16(a, b);
   const float a1 = a - __builtin_bit_cast(float, h << 16);
   const float b1 = b - __builtin_bit_cast(float, h & 0xffff0000u);
@@ -38,14 +51,11 @@ __device__ __forceinline__ void split3(float a, float b, unsigned& h, unsigned& 
 constexpr int PART_A[6] = {2, 0, 1, 1, 0, 0}, PART_B[6] = {0, 2, 1, 0, 1, 0};
 
 // Whether a sum of six products cannot be trusted.  An operand that is not
-// finite, or that rounds to infinity in bf16, leaves a NaN or an infinity in
-// every sum it enters; operands so small that their last parts are below the
-// smallest normal number, which the matrix cores read as zeros, leave a tiny
-// sum.  Such sums are formed again on the fp32 matrix cores.
-constexpr float PARTS_TINY = 8.271806e-25f;   // 2^-80
+// finite, or that rounds to infinity in bf16 once scaled (from 2^105 on),
+// leaves a NaN or an infinity in every sum it enters, as does a sum past 2^82.
+// Such sums are formed again on the fp32 matrix cores.
 __device__ __forceinline__ bool parts_doubtful(float sum) {
-  const float c = fabsf(sum);
-  return !(c < __builtin_inff()) || (c > 0.f && c < PARTS_TINY);
+  return !(fabsf(sum) < __builtin_inff());
 }
 
 }  // namespace nf

@@ -746,7 +746,10 @@ __device__ __forceinline__ void fwd_skinny_tile(const GemmParamsT<float>& p, int
   for (int u = 0; u < NW; ++u) {
     acc[u] += small[u];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) bad |= parts_doubtful(acc[u][v]);
+    for (int v = 0; v < 4; ++v) {
+      bad |= parts_doubtful(acc[u][v]);
+      acc[u][v] *= PARTS_UNSCALE;
+    }
   }
   if (__any(bad)) {
     // this wave's block again in fp32: input 4 j + g of lane (r, g)

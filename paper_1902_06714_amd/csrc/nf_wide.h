@@ -15,7 +15,7 @@
 //
 // What bounds it: on large problems the power limit (8192 x 4096 x 4096 runs
 // at 1.7 - 1.9 GHz with the matrix cores 70% busy), else the vector
-// instructions of the split, 11 for two values, which a wave does not overlap
+// instructions of the split, 13 for two values, which a wave does not overlap
 // with its own matrix instructions (a second wave on the SIMD does: per
 // matrix instruction 39 clocks alone, 64 with four vector instructions in the
 // same wave, 43 with them in another).  Hence tiles as large as the grid
@@ -354,16 +354,20 @@ __device__ __forceinline__ void clear(floatx16 (&acc)[TM][TN]) {
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 }
 
-// Whether any of the sums cannot be trusted.
+// The scale of the parts taken out of the sums, and whether any of them cannot
+// be trusted.
 template <int TM, int TN>
-__device__ __forceinline__ bool doubtful(const floatx16 (&acc)[TM][TN]) {
+__device__ __forceinline__ bool unscale(floatx16 (&acc)[TM][TN]) {
   bool bad = false;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) bad |= parts_doubtful(acc[i][j][v]);
+      for (int v = 0; v < 16; ++v) {
+        bad |= parts_doubtful(acc[i][j][v]);
+        acc[i][j][v] *= PARTS_UNSCALE;
+      }
   return bad;
 }
 
@@ -474,7 +478,7 @@ __device__ __forceinline__ void wide_tile(const GemmParamsT<float>& p, int bx, i
   // the order of a stage's instructions: matrix instructions with the LDS
   // accesses and a share of the vector instructions between them
   constexpr int NM = 6 * TM * TN, NR = 3 * (TM + TN);
-  constexpr int NV = 22 * (LA::Q + LB::Q) + (DW ? 4 * LA::Q : 0) + 16;
+  constexpr int NV = 26 * (LA::Q + LB::Q) + (DW ? 4 * LA::Q : 0) + 16;
   constexpr int VPM = (NV + NM - 1) / NM;
   // FD: stage t's operands are in fragment set t & 1, stage t + 1 in LDS
   // buffer (t + 1) & 1, stages t + 2 and t + 3 in the register sets (stage s
@@ -557,7 +561,7 @@ __device__ __forceinline__ void wide_tile(const GemmParamsT<float>& p, int bx, i
 #pragma unroll
       for (int j = 0; j < TN; ++j) acc[i][j] += small[i][j];
   }
-  if (__syncthreads_or(doubtful(acc))) {
+  if (__syncthreads_or(unscale(acc))) {
     float* const as = reinterpret_cast<float*>(lds);
     float* const bs = as + BK * BM;
     clear(acc);
@@ -699,7 +703,7 @@ __device__ __forceinline__ void wide_tile_roles(const GemmParamsT<float>& p, int
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] += small[i][j];
-  if (__any(doubtful(acc)) && lane == 0) *again = 1;
+  if (__any(unscale(acc)) && lane == 0) *again = 1;
   __syncthreads();
   if (*again) {
     const float* const as = reinterpret_cast<const float*>(lds);

@@ -1,0 +1,171 @@
+"""The range of the fp32 products that are formed from three bf16 parts per
+operand: small operands beside large partners, subnormal operands and long sums of
+them give what fp32 arithmetic gives, in every kernel that splits its operands.
+
+Bound: an fp32 sum of k products of the absolute values, and a rounding to the
+smallest subnormal number.  The large partners keep every sum far from underflow."""
+
+import numpy as np
+import pytest
+
+from .gpu_run import note, torch_cuda
+
+pytestmark = pytest.mark.gpu
+
+
+def _net(dims, acts, theta):
+    from paper_1902_06714_amd import nf
+    h = nf.nf_net_create(dims, list(acts))
+    nf.nf_set_params(h, np.concatenate([np.asarray(t.cpu() if hasattr(t, "cpu") else t).ravel()
+                                        for t in theta]).astype(np.float32))
+    return nf, h
+
+
+def _names(nf, h, call):
+    nf.nf_profile(h, 1)
+    call()
+    names = {k["name"] for k in nf.nf_profile_read(h)}
+    nf.nf_profile(h, 0)
+    return names
+
+
+def _rand(torch, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    return lambda *s: torch.rand(*s, generator=g, device="cuda") + 0.5
+
+
+def _check(torch, got, a, b):
+    """got against a @ b, a and b the fp32 operands."""
+    a, b = a.double(), b.double()
+    ref = a @ b
+    bound = (a.shape[1] + 2) * 2.0 ** -24 * (a.abs() @ b.abs()) + 2.0 ** -149
+    off = ((got.double() - ref).abs() - bound).max().item()
+    assert off <= 0, (off, ((got.double() - ref).norm() / ref.norm()).item())
+
+
+# rows of the small operand, as powers of ten: below 2^-108 the third part was lost, below
+# 2^-117 the second, below 2^-126 all; the last are a few times 2^-149
+SMALL = [-33, -34, -35, -36, -37, -38, -39, -41, -44]
+
+
+def _small_rows(torch, x):
+    scale = torch.tensor([10.0 ** e for e in SMALL], dtype=torch.float64, device="cuda")
+    reps = (x.shape[0] + len(SMALL) - 1) // len(SMALL)
+    return (x.double() * scale.repeat(reps)[:x.shape[0], None]).float()
+
+
+# (rows, k, units) and the tile that must run
+FORWARD = [
+    ((70, 203, 150), "wide_fwd_out_64x64"),
+    ((64, 2048, 200), "wide_fwd_piece_64x64"),
+    ((4352, 64, 4352), "wide_fwd_out_128x128"),
+    ((4096, 1024, 4096), "wide_fwd_out_256x256"),
+]
+
+
+@pytest.mark.parametrize("shape,kernel", FORWARD)
+@pytest.mark.parametrize("side", ["samples", "weights"])
+def test_forward(shape, kernel, side):
+    torch = torch_cuda()
+    m, k, n = shape
+    rand = _rand(torch, m + k)
+    x, w = rand(m, k), rand(n, k)
+    if side == "samples":
+        x, w = _small_rows(torch, x), 1e30 * w
+    else:
+        x, w = 1e30 * x, _small_rows(torch, w)
+    out = torch.empty(m, n, device="cuda")
+    nf, h = _net((k, n), ("relu",), (w, np.zeros(n)))
+    try:
+        note(f"small operands forward {shape} {side}")
+        assert kernel in _names(nf, h, lambda: nf.nf_forward(h, x, out))
+    finally:
+        nf.nf_net_destroy(h)
+    _check(torch, out, x, w.t().contiguous())
+
+
+@pytest.mark.parametrize("m,k,n", [(33, 40, 17), (40, 785, 100), (3000, 129, 128), (10000, 784, 100)])
+@pytest.mark.parametrize("side", ["samples", "weights"])
+def test_forward_skinny(m, k, n, side):
+    """Through a second layer that passes the first one's values on."""
+    torch = torch_cuda()
+    rand = _rand(torch, m + k)
+    x, w = rand(m, k), rand(n, k)
+    if side == "samples":
+        x, w = _small_rows(torch, x), 1e30 * w
+    else:
+        x, w = 1e30 * x, _small_rows(torch, w)
+    out = torch.empty(m, n, device="cuda")
+    # (several units, so that the net is not a narrow one)
+    wide = max(n, 40)
+    w1 = torch.zeros(wide, k, device="cuda")
+    w1[:n] = w
+    w2 = torch.zeros(n, wide, device="cuda")
+    w2[torch.arange(n), torch.arange(n)] = 1
+    nf, h = _net((k, wide, n), ("relu",), (w1, np.zeros(wide), w2, np.zeros(n)))
+    try:
+        note(f"small operands skinny {m} {k} {n} {side}")
+        assert "fwd_skinny" in _names(nf, h, lambda: nf.nf_forward(h, x, out))
+    finally:
+        nf.nf_net_destroy(h)
+    _check(torch, out, x, w.t().contiguous())
+
+
+# (batch, inputs, units) and the tile
+TENDENCIES = [
+    ((203, 70, 150), "wide_dw_sgd_64x64"),
+    ((2100, 200, 300), "wide_dw_partial_64x64"),
+    ((256, 2048, 2048), "wide_dw_sgd_128x128"),
+    ((1024, 4096, 4096), "wide_dw_sgd_256x256"),
+]
+
+
+@pytest.mark.parametrize("shape,kernel", TENDENCIES)
+def test_tendencies(shape, kernel):
+    """One relu layer without weights: its deltas are its biases minus the targets."""
+    torch = torch_cuda()
+    b, k, n = shape
+    rand = _rand(torch, b + k)
+    bias = torch.full((n,), 1e-44, device="cuda")
+    y = -_small_rows(torch, rand(n, b)).t().contiguous()
+    x = 1e30 * rand(b, k)
+    nf, h = _net((k, n), ("relu",), (np.zeros(n * k), bias))
+    try:
+        note(f"small operands tendencies {shape}")
+        assert kernel in _names(nf, h, lambda: nf.nf_train_batch(h, x, y, 0.0, 1))
+        got = torch.from_numpy(nf.nf_get_grads(h)[:n * k]).cuda().view(n, k)
+    finally:
+        nf.nf_net_destroy(h)
+    _check(torch, got, (bias - y).t().contiguous(), x)
+
+
+# (batch = inputs, hidden units, outputs) and the tile
+DELTAS = [
+    ((70, 150, 203), "wide_bwd_64x64"),
+    ((33, 400, 700), "wide_bwd_piece_64x64"),
+    ((2048, 2048, 200), "wide_bwd_128x128"),
+    ((4096, 4096, 1024), "wide_bwd_256x256"),
+]
+
+
+@pytest.mark.parametrize("shape,kernel", DELTAS)
+def test_deltas(shape, kernel):
+    """A tanh layer at zero, whose f' is 1, below a relu layer whose deltas are
+    its biases minus the targets; unit samples make the first layer's
+    tendencies its deltas."""
+    torch = torch_cuda()
+    b, n1, n2 = shape
+    rand = _rand(torch, b + n1)
+    bias = torch.full((n2,), 1e-44, device="cuda")
+    y = -_small_rows(torch, rand(b, n2))
+    w2 = 1e30 * rand(n2, n1)
+    x = torch.eye(b, device="cuda")
+    nf, h = _net((b, n1, n2), ("tanh", "relu"), (np.zeros(n1 * b), np.zeros(n1), w2, bias))
+    try:
+        note(f"small operands deltas {shape}")
+        assert kernel in _names(nf, h, lambda: nf.nf_train_batch(h, x, y, 0.0, 1))
+        got = torch.from_numpy(nf.nf_get_grads(h)[:n1 * b]).cuda().view(n1, b)
+    finally:
+        nf.nf_net_destroy(h)
+    _check(torch, got.t(), bias - y, w2)
