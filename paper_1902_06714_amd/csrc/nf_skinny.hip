@@ -752,9 +752,11 @@ __device__ __forceinline__ void fwd_skinny_tile(const GemmParamsT<float>& p, int
     }
   }
   if (__any(bad)) {
-    // this wave's block again in fp32: input 4 j + g of lane (r, g)
+    // this wave's block again in fp32, for the sums that cannot be trusted:
+    // input 4 j + g of lane (r, g)
+    floatx4 f32[NW];
 #pragma unroll
-    for (int u = 0; u < NW; ++u) acc[u] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int u = 0; u < NW; ++u) f32[u] = floatx4{0.f, 0.f, 0.f, 0.f};
     for (int k = gq; k < ((kend - kbeg + 3) & ~3); k += 4) {
       const bool ok = k < kend - kbeg;
       const float a = sk_load1(ra, ok && xok ? 4u * (unsigned)(r * lda + k) : SK_OOB);
@@ -762,9 +764,13 @@ __device__ __forceinline__ void fwd_skinny_tile(const GemmParamsT<float>& p, int
       for (int u = 0; u < NW; ++u) {
         const int n = 16 * (ub + u) + r;
         const float w = sk_load1(rb, ok && n < N ? 4u * (unsigned)(n * ldb + k) : SK_OOB);
-        acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, w, acc[u], 0, 0, 0);
+        f32[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, w, f32[u], 0, 0, 0);
       }
     }
+#pragma unroll
+    for (int u = 0; u < NW; ++u)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[u][v] = parts_doubtful(acc[u][v]) ? f32[u][v] : acc[u][v];
   }
 
   // accumulator register v of lane (r, gq): sample s0 + 4 gq + v, unit 16 u + r

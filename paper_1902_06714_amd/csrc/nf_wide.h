@@ -38,9 +38,9 @@ namespace nf {
 
 constexpr int WIDE_KI = 16;      // k of one 32x32x16 matrix instruction
 
-// bytes of LDS: nb stages, and a flag
+// bytes of LDS: nb stages
 constexpr int wide_lds(int BM, int BN, int BK, int nb) {
-  return nb * 3 * (BK / 8) * ((BM + BN) * 16 + 256) + 16;
+  return nb * 3 * (BK / 8) * ((BM + BN) * 16 + 256);
 }
 
 // Global -> registers -> LDS of one R x BK operand tile X(r, k) by NT threads,
@@ -118,14 +118,6 @@ struct SplitLoader {
               float, __builtin_amdgcn_raw_buffer_load_b32(rs, at + (unsigned)(c * ldi) * 4u, 0, 0));
       }
     }
-  }
-
-  // the values as they are, lds[k][r]
-  __device__ __forceinline__ void store_f32(float* lds, int tid) const {
-#pragma unroll
-    for (int i = 0; i < Q; ++i)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) lds[(kof(tid, i) + c) * R + row(tid, i)] = v[4 * i + c];
   }
 
   // each quad's values added to its sum (in the tendencies the sums over the
@@ -354,41 +346,69 @@ __device__ __forceinline__ void clear(floatx16 (&acc)[TM][TN]) {
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 }
 
-// The scale of the parts taken out of the sums, and whether any of them cannot
-// be trusted.
-template <int TM, int TN>
-__device__ __forceinline__ bool unscale(floatx16 (&acc)[TM][TN]) {
-  bool bad = false;
+// A lane's values of 16 k of an operand X(r, k) for eight 32x32x2 fp32
+// instructions: row r0 + lane % 32, k0 + 8 q + 4 (lane / 32) + c for instruction 4 q
+// + c, zeros past the last row and the last k (`left` of them from k0).
+template <bool KC>
+__device__ __forceinline__ void row_values(const float* X, int64_t ld, int r0, int rmax, int k0,
+                                           int left, int lane, float (&x)[8]) {
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(X + (KC ? (int64_t)r0 * ld + k0 : (int64_t)k0 * ld + r0)), (short)0, (int)TILE_OOB,
+      0x00020000);
+  const int r = lane & 31, h = 4 * (lane >> 5);
+  const bool ok = r0 + r < rmax;
+  if (KC && left >= 16) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const floatx4 u = __builtin_bit_cast(
+          floatx4, __builtin_amdgcn_raw_buffer_load_b128(
+                       rs, ok ? (unsigned)(r * (int)ld + 8 * q + h) * 4u : TILE_OOB, 0, 0));
+#pragma unroll
+      for (int c = 0; c < 4; ++c) x[4 * q + c] = u[c];
+    }
+  } else {
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const int k = 8 * (s >> 2) + h + (s & 3);
+      x[s] = get(rs, ok && k < left ? (unsigned)(KC ? r * (int)ld + k : k * (int)ld + r) * 4u : TILE_OOB);
+    }
+  }
+}
+
+// The scale of the parts taken out of a wave's sums.  A block with sums that
+// cannot be trusted is formed again on the fp32 matrix cores, straight from
+// memory (the 32x32x2 instruction shares the accumulators' layout), and those
+// sums, and no others, are replaced: each depends on its own row and column
+// alone.
+template <bool AKC, bool BKC, int TM, int TN>
+__device__ __forceinline__ void finish_sums(const GemmParamsT<float>& p, floatx16 (&acc)[TM][TN], int m0,
+                                            int n0, int wm, int wn, int kbeg, int kend, int lane) {
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int j = 0; j < TN; ++j) {
+      bool bad = false;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         bad |= parts_doubtful(acc[i][j][v]);
         acc[i][j][v] *= PARTS_UNSCALE;
       }
-  return bad;
-}
-
-// The fp32 products of one stage held in LDS as [BK][BM] and [BK][BN]: the
-// 32x32x2 fp32 instruction shares the accumulators' layout.
-template <int BM, int BN, int BK, int TM, int TN>
-__device__ __forceinline__ void multiply_f32(const float* as, const float* bs, floatx16 (&acc)[TM][TN],
-                                             int wm, int wn, int lane) {
+      if (__any(bad)) {
+        const int m = m0 + wm + i * 32, n = n0 + wn + j * 32;
+        floatx16 f32 = {};
 #pragma unroll 1
-  for (int k = lane >> 5; k < BK; k += 2) {
-    float x[TM], y[TN];
+        for (int k0 = kbeg; k0 < kend; k0 += 16) {
+          float x[8], y[8];
+          row_values<AKC>(p.A, p.lda, m, p.M, k0, kend - k0, lane, x);
+          row_values<BKC>(p.B, p.ldb, n, p.N, k0, kend - k0, lane, y);
 #pragma unroll
-    for (int i = 0; i < TM; ++i) x[i] = as[k * BM + wm + i * 32 + (lane & 31)];
+          for (int s = 0; s < 8; ++s) f32 = __builtin_amdgcn_mfma_f32_32x32x2f32(x[s], y[s], f32, 0, 0, 0);
+        }
 #pragma unroll
-    for (int j = 0; j < TN; ++j) y[j] = bs[k * BN + wn + j * 32 + (lane & 31)];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[i], y[j], acc[i][j], 0, 0, 0);
-  }
+        for (int v = 0; v < 16; ++v)
+          acc[i][j][v] = parts_doubtful(acc[i][j][v]) ? f32[v] : acc[i][j][v];
+      }
+    }
 }
 
 // The bias tendencies of a tile's rows from the sums of the quads of k that
@@ -428,8 +448,7 @@ __device__ __forceinline__ void wide_tile(const GemmParamsT<float>& p, int bx, i
   typedef SplitLoader<BM, BK, NT, AKC, AV> LA;
   typedef SplitLoader<BN, BK, NT, BKC, BV> LB;
   constexpr int STAGE = 3 * (LA::PART + LB::PART);
-  static_assert(2 * STAGE <= wide_lds(BM, BN, BK, 2), "LDS size");
-  static_assert(BK * (BM + BN) * 4 <= 2 * STAGE, "LDS size");
+  static_assert(2 * STAGE == wide_lds(BM, BN, BK, 2), "LDS size");
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -561,24 +580,12 @@ __device__ __forceinline__ void wide_tile(const GemmParamsT<float>& p, int bx, i
 #pragma unroll
       for (int j = 0; j < TN; ++j) acc[i][j] += small[i][j];
   }
-  if (__syncthreads_or(unscale(acc))) {
-    float* const as = reinterpret_cast<float*>(lds);
-    float* const bs = as + BK * BM;
-    clear(acc);
-    for (int t = 0; t < ntiles; ++t) {
-      request(0, t);
-      la[0].store_f32(as, tid);
-      lb[0].store_f32(bs, tid);
-      __syncthreads();
-      multiply_f32<BM, BN, BK>(as, bs, acc, wm, wn, lane);
-      __syncthreads();
-    }
-  }
-  wide_epilogue<BM, TM, TN, EPI>(p, acc, m0, n0, wm, wn, lane, bz);
   if constexpr (DW) {
     if (by == 0)
       put_bias_sums<LA, BM, BK, EPI>(p, bsum, m0, bz, tid, reinterpret_cast<float*>(lds));
   }
+  finish_sums<AKC, BKC>(p, acc, m0, n0, wm, wn, kbeg, kend, lane);
+  wide_epilogue<BM, TM, TN, EPI>(p, acc, m0, n0, wm, wn, lane, bz);
 }
 
 // The same by (BM / WM) x (BN / WN) waves that multiply and NP more that load,
@@ -592,9 +599,7 @@ __device__ __forceinline__ void wide_tile_roles(const GemmParamsT<float>& p, int
   typedef SplitLoader<BM, BK, NT, AKC, AV> LA;
   typedef SplitLoader<BN, BK, NT, BKC, BV> LB;
   constexpr int STAGE = 3 * (LA::PART + LB::PART);
-  static_assert(NB * STAGE + 16 == wide_lds(BM, BN, BK, NB), "LDS size");
-  static_assert(BK * (BM + BN) * 4 <= NB * STAGE, "LDS size");
-  volatile int* const again = reinterpret_cast<volatile int*>(lds + NB * STAGE);
+  static_assert(NB * STAGE == wide_lds(BM, BN, BK, NB), "LDS size");
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
@@ -605,8 +610,7 @@ __device__ __forceinline__ void wide_tile_roles(const GemmParamsT<float>& p, int
   constexpr bool DW = EPI == EPI_DW_SGD || EPI == EPI_DW_PARTIAL;
 
   // Both roles meet at the same barriers: one before the first stage, one
-  // after each stage, one for the check of the sums, two for each stage done
-  // again, one for the bias sums.
+  // after each stage, one for the bias sums.
   if (wave >= NC) {
     const int tid = threadIdx.x - NC * 64;
     LA la[NB];
@@ -629,7 +633,6 @@ __device__ __forceinline__ void wide_tile_roles(const GemmParamsT<float>& p, int
     request(0, NB);
     deliver(1);
     request(1, NB + 1);
-    if (tid == 0) *again = 0;
     __syncthreads();
     for (int t = 0; t < ntiles; t += NB) {
 #pragma unroll
@@ -638,17 +641,6 @@ __device__ __forceinline__ void wide_tile_roles(const GemmParamsT<float>& p, int
         const int set = (d + 2) % NB;
         deliver(set);
         request(set, t + d + 2 + NB);
-        __syncthreads();
-      }
-    }
-    __syncthreads();
-    if (*again) {
-      float* const as = reinterpret_cast<float*>(lds);
-      for (int t = 0; t < ntiles; ++t) {
-        request(0, t);
-        la[0].store_f32(as, tid);
-        lb[0].store_f32(as + BK * BM, tid);
-        __syncthreads();
         __syncthreads();
       }
     }
@@ -703,17 +695,7 @@ __device__ __forceinline__ void wide_tile_roles(const GemmParamsT<float>& p, int
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] += small[i][j];
-  if (__any(unscale(acc)) && lane == 0) *again = 1;
-  __syncthreads();
-  if (*again) {
-    const float* const as = reinterpret_cast<const float*>(lds);
-    clear(acc);
-    for (int t = 0; t < ntiles; ++t) {
-      __syncthreads();
-      multiply_f32<BM, BN, BK>(as, as + BK * BM, acc, wm, wn, lane);
-      __syncthreads();
-    }
-  }
+  finish_sums<AKC, BKC>(p, acc, m0, n0, wm, wn, kbeg, kend, lane);
   if constexpr (DW) {
     if (by == 0) __syncthreads();
   }

@@ -68,5 +68,4 @@ def test_rows_do_not_leak(dims, batch):
     note(f"row leak dims={dims} batch={batch}")
     rest = np.setdiff1d(np.arange(batch), bad)
     assert np.isnan(out[bad]).all()
-    # (rows that share a block with a NaN are formed on the fp32 matrix cores)
     assert np.max(np.abs(out[rest] - clean[rest])) < 2e-5

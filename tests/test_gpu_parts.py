@@ -169,3 +169,44 @@ def test_deltas(shape, kernel):
     finally:
         nf.nf_net_destroy(h)
     _check(torch, got.t(), bias - y, w2)
+
+
+# rows of the batch that the parts cannot hold: sums of them are formed again
+BAD = [np.nan, np.inf, 3e38, 1e35]
+
+# (dims, batch, kernel): each tile, and the skinny forward kernel
+NEIGHBOURS = [
+    ((203, 150), 70, "wide_fwd_out_64x64"),
+    ((2048, 200), 64, "wide_fwd_piece_64x64"),
+    ((64, 4352), 4352, "wide_fwd_out_128x128"),
+    ((1024, 4096), 4096, "wide_fwd_out_256x256"),
+    ((129, 77, 33, 5), 40, "fwd_skinny"),
+    ((784, 100, 10), 10000, "fwd_skinny"),
+]
+
+
+@pytest.mark.parametrize("dims,batch,kernel", NEIGHBOURS)
+def test_neighbours(dims, batch, kernel):
+    """A sample's outputs are the same bits whatever the samples beside it hold."""
+    torch = torch_cuda()
+    rand = _rand(torch, batch)
+    theta = []
+    for a, b in zip(dims, dims[1:]):
+        theta += [(rand(b, a) - 1) / a ** 0.5, rand(b)]
+    x = rand(batch, dims[0])
+    bad = torch.arange(1, batch, 5, device="cuda")
+    y = x.clone()
+    y[bad, 3] = torch.tensor(BAD, device="cuda").repeat(bad.numel())[:bad.numel()]
+    out, out2 = (torch.empty(batch, dims[-1], device="cuda") for _ in range(2))
+    nf, h = _net(dims, ("tanh",), theta)
+    try:
+        note(f"neighbours {dims} {batch}")
+        assert kernel in _names(nf, h, lambda: nf.nf_forward(h, x, out))
+        nf.nf_forward(h, y, out2)
+        torch.cuda.synchronize()
+    finally:
+        nf.nf_net_destroy(h)
+    rest = torch.ones(batch, dtype=torch.bool, device="cuda")
+    rest[bad] = False
+    assert torch.isnan(out2[bad[::4]]).all()
+    assert torch.equal(out[rest], out2[rest])
