@@ -37,10 +37,12 @@
 namespace nf {
 
 constexpr int WIDE_KI = 16;      // k of one 32x32x16 matrix instruction
+constexpr int WIDE_ROLES_BK = 32;   // k of a stage of the tiles with loading waves
 
-// bytes of LDS: nb stages
+// bytes of LDS of 8 k of R rows, and of nb stages of BK
+constexpr int wide_half(int R, int BK) { return R * 16 + (BK > 16 ? 64 : 128); }
 constexpr int wide_lds(int BM, int BN, int BK, int nb) {
-  return nb * 3 * (BK / 8) * ((BM + BN) * 16 + 256);
+  return nb * 3 * (BK / 8) * (wide_half(BM, BK) + wide_half(BN, BK));
 }
 
 // Global -> registers -> LDS of one R x BK operand tile X(r, k) by NT threads,
@@ -58,7 +60,7 @@ constexpr int wide_lds(int BM, int BN, int BK, int nb) {
 template <int R, int BK, int NT, bool KC, bool VEC>
 struct SplitLoader {
   static constexpr int Q = R * BK / (4 * NT);
-  static constexpr int HALF = R * 16 + 128;      // bytes of 8 k of every row
+  static constexpr int HALF = wide_half(R, BK);  // bytes of 8 k of every row
   static constexpr int PART = BK / 8 * HALF;     // bytes of one part
   static_assert(Q >= 1 && Q * 4 * NT == R * BK, "whole quads");
   static constexpr int C = KC || Q == 1 ? 1 : 2; // quads of a run of k
@@ -218,25 +220,42 @@ __device__ __forceinline__ void with_input(const __amdgpu_buffer_rsrc_t& r, int6
 }
 
 
+// The biases of a wave's columns, requested before the products so that a small
+// launch does not wait for them after.
+template <int TN, int EPI>
+struct Biases {
+  float b[TN];
+  __device__ __forceinline__ Biases(const GemmParamsT<float>& p, int n0, int wn, int lane) {
+    if constexpr (EPI == EPI_FWD_STASH || EPI == EPI_FWD_OUT || EPI == EPI_FWD_DELTA) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int n = n0 + wn + j * 32 + (lane & 31);
+        b[j] = n < p.N ? p.bias[n] : 0.f;
+      }
+    }
+  }
+};
+
 template <int BM, int TM, int TN, int EPI, int ACT>
 __device__ __forceinline__ void forward_epilogue(const GemmParamsT<float>& p, floatx16 (&acc)[TM][TN],
-                                                 int m0, int n0, int wm, int wn, int lane) {
-  float bias[TN];
-#pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const int n = n0 + wn + j * 32 + (lane & 31);
-    bias[j] = n < p.N ? p.bias[n] : 0.f;
-  }
+                                                 const float (&bias)[TN], int m0, int n0, int wm, int wn,
+                                                 int lane) {
   const __amdgpu_buffer_rsrc_t r0 = tile_rows(p.out0, p.ld0, m0, p.M, BM);
   // out1 has out0's pitch (the host checks)
   const __amdgpu_buffer_rsrc_t r1 = tile_rows(EPI == EPI_FWD_STASH ? p.out1 : p.out0, p.ld0, m0, p.M, BM);
   each_block<TM, TN>(p.ld0, n0, p.N, wm, wn, lane, [&](int i, int j, auto off) {
+    // 8 rows at a time, those past the matrix left out: a small batch waits for
+    // every activation (one sample, 8 inputs, 300 units: 5.9 us with all, 4.3)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      float f, fp;
-      act_eval<float>(ACT, acc[i][j][v] + bias[j], f, fp);
-      put(r0, off(v), f);
-      if constexpr (EPI == EPI_FWD_STASH) put(r1, off(v), fp);
+    for (int q = 0; q < 4; ++q) {
+      if (i * 32 + 8 * q >= p.M - m0 - wm) break;
+#pragma unroll
+      for (int v = 4 * q; v < 4 * q + 4; ++v) {
+        float f, fp;
+        act_eval<float>(ACT, acc[i][j][v] + bias[j], f, fp);
+        put(r0, off(v), f);
+        if constexpr (EPI == EPI_FWD_STASH) put(r1, off(v), fp);
+      }
     }
   });
 }
@@ -244,13 +263,13 @@ __device__ __forceinline__ void forward_epilogue(const GemmParamsT<float>& p, fl
 // The output delta: the targets' rows have a pitch of their own.
 template <int BM, int TM, int TN, int ACT>
 __device__ __forceinline__ void delta_epilogue(const GemmParamsT<float>& p, floatx16 (&acc)[TM][TN],
-                                               int m0, int n0, int wm, int wn, int lane) {
+                                               const float (&bias)[TN], int m0, int n0, int wm, int wn,
+                                               int lane) {
   const __amdgpu_buffer_rsrc_t r0 = tile_rows(p.out0, p.ld0, m0, p.M, BM);
   const __amdgpu_buffer_rsrc_t ry = tile_rows(p.aux, p.ldaux, m0, p.M, BM);
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
     const int n = n0 + wn + j * 32 + (lane & 31), row = wm + 4 * (lane >> 5);
-    const float bias = n < p.N ? p.bias[n] : 0.f;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       float y[16];
@@ -260,11 +279,15 @@ __device__ __forceinline__ void delta_epilogue(const GemmParamsT<float>& p, floa
         y[v] = get(ry, n < p.N ? (unsigned)(m * (int)p.ldaux + n) * 4u : TILE_OOB);
       }
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int m = row + i * 32 + 8 * (v >> 2) + (v & 3);
-        float f, fp;
-        act_eval<float>(ACT, acc[i][j][v] + bias, f, fp);
-        put(r0, n < p.N ? (unsigned)(m * (int)p.ld0 + n) * 4u : TILE_OOB, (f - y[v]) * fp);
+      for (int q = 0; q < 4; ++q) {
+        if (i * 32 + 8 * q >= p.M - m0 - wm) break;
+#pragma unroll
+        for (int v = 4 * q; v < 4 * q + 4; ++v) {
+          const int m = row + i * 32 + 8 * q + (v & 3);
+          float f, fp;
+          act_eval<float>(ACT, acc[i][j][v] + bias[j], f, fp);
+          put(r0, n < p.N ? (unsigned)(m * (int)p.ld0 + n) * 4u : TILE_OOB, (f - y[v]) * fp);
+        }
       }
     }
   }
@@ -272,14 +295,15 @@ __device__ __forceinline__ void delta_epilogue(const GemmParamsT<float>& p, floa
 
 template <int BM, int TM, int TN, int EPI>
 __device__ __forceinline__ void wide_epilogue(const GemmParamsT<float>& p, floatx16 (&acc)[TM][TN],
-                                              int m0, int n0, int wm, int wn, int lane, int bz) {
+                                              const Biases<TN, EPI>& bias, int m0, int n0, int wm, int wn,
+                                              int lane, int bz) {
   if constexpr (EPI == EPI_FWD_STASH || EPI == EPI_FWD_OUT || EPI == EPI_FWD_DELTA) {
     // one switch per tile, not one per entry
     auto emit = [&](auto act) {
       if constexpr (EPI == EPI_FWD_DELTA)
-        delta_epilogue<BM, TM, TN, act.value>(p, acc, m0, n0, wm, wn, lane);
+        delta_epilogue<BM, TM, TN, act.value>(p, acc, bias.b, m0, n0, wm, wn, lane);
       else
-        forward_epilogue<BM, TM, TN, EPI, act.value>(p, acc, m0, n0, wm, wn, lane);
+        forward_epilogue<BM, TM, TN, EPI, act.value>(p, acc, bias.b, m0, n0, wm, wn, lane);
     };
     switch (p.act) {
       case ACT_GAUSSIAN: emit(std::integral_constant<int, ACT_GAUSSIAN>()); break;
@@ -465,6 +489,7 @@ __device__ __forceinline__ void wide_tile(const GemmParamsT<float>& p, int bx, i
   // the registers hold both (not in the 256 x 256 tile): the sum of hh is
   // rounded once for 16 k, not six times
   constexpr bool APART = TM * TN <= 4;
+  const Biases<TN, EPI> bias(p, n0, wn, lane);
   floatx16 acc[TM][TN], small[APART ? TM : 1][APART ? TN : 1];
   clear(acc);
   clear(small);
@@ -568,9 +593,10 @@ __device__ __forceinline__ void wide_tile(const GemmParamsT<float>& p, int bx, i
     for (int i = 0; i < TM; ++i) fetch_a(0, i, lds);
   }
   __syncthreads();
-  // (an odd last stage is followed by one of zeros)
+  // (an odd last stage is followed by one of zeros, but in the smallest tile)
   for (int t = 0; t < ntiles; t += 2) {
     stage(0, t);
+    if (BM == 64 && t + 1 == ntiles) break;
     stage(1, t + 1);
   }
 
@@ -585,17 +611,24 @@ __device__ __forceinline__ void wide_tile(const GemmParamsT<float>& p, int bx, i
       put_bias_sums<LA, BM, BK, EPI>(p, bsum, m0, bz, tid, reinterpret_cast<float*>(lds));
   }
   finish_sums<AKC, BKC>(p, acc, m0, n0, wm, wn, kbeg, kend, lane);
-  wide_epilogue<BM, TM, TN, EPI>(p, acc, m0, n0, wm, wn, lane, bz);
+  wide_epilogue<BM, TM, TN, EPI>(p, acc, bias, m0, n0, wm, wn, lane, bz);
 }
 
 // The same by (BM / WM) x (BN / WN) waves that multiply and NP more that load,
-// for the tiles too small to hide the one behind the other within a wave.
+// for the tiles too small to hide the one behind the other within a wave.  A
+// stage is 32 k: a small grid runs at the pace of the chain load - split - LDS -
+// barrier, which two loading waves for each multiplying one and half as many
+// barriers make half as long (64 x 64 tile, a stage of 16 k and one loading
+// wave each before: a k of 16 took 0.38 us alone, 0.19 now; 16 x 255 x 300 10.0
+// us, 7.4; 1024 x 1024 x 1000 28.7, 22.6).  Two workgroups fit on a CU (78 KB of
+// LDS and at most 80 registers each), which large grids need.
 template <int BM, int BN, int WM, int WN, int NP, bool AKC, bool BKC, bool AV, bool BV, int EPI>
 __device__ __forceinline__ void wide_tile_roles(const GemmParamsT<float>& p, int bx, int by, int bz,
                                                 char* lds) {
   constexpr int NC = (BM / WM) * (BN / WN);    // waves that multiply
   constexpr int NT = NP * 64;                  // threads that load
-  constexpr int TM = WM / 32, TN = WN / 32, BK = WIDE_KI, NB = 3;
+  constexpr int TM = WM / 32, TN = WN / 32, BK = WIDE_ROLES_BK, NB = 3, NR = 3, KS = BK / WIDE_KI;
+  static_assert(NR % NB == 0 && KS % 2 == 0, "the loops are unrolled by the sets of registers");
   typedef SplitLoader<BM, BK, NT, AKC, AV> LA;
   typedef SplitLoader<BN, BK, NT, BKC, BV> LB;
   constexpr int STAGE = 3 * (LA::PART + LB::PART);
@@ -613,34 +646,34 @@ __device__ __forceinline__ void wide_tile_roles(const GemmParamsT<float>& p, int
   // after each stage, one for the bias sums.
   if (wave >= NC) {
     const int tid = threadIdx.x - NC * 64;
-    LA la[NB];
-    LB lb[NB];
+    LA la[NR];
+    LB lb[NR];
     float bsum[LA::Q] = {};
     auto request = [&](int set, int t) {
       la[set].load(p.A, p.lda, p.M, kend, m0, kbeg + t * BK, tid);
       lb[set].load(p.B, p.ldb, p.N, kend, n0, kbeg + t * BK, tid);
     };
-    auto deliver = [&](int set) {
-      la[set].store(lds + set * STAGE, tid);
-      lb[set].store(lds + set * STAGE + 3 * LA::PART, tid);
+    auto deliver = [&](int set, int buf) {
+      la[set].store(lds + buf * STAGE, tid);
+      lb[set].store(lds + buf * STAGE + 3 * LA::PART, tid);
       if constexpr (DW) la[set].add_up(bsum);
     };
-    // stage s passes through register set and LDS buffer s % NB; while stage
-    // t is multiplied stage t + 2 is delivered
+    // stage s passes through register set s % NR and LDS buffer s % NB; while
+    // stage t is multiplied stage t + 2 is delivered
 #pragma unroll
-    for (int d = 0; d < NB; ++d) request(d, d);
-    deliver(0);
-    request(0, NB);
-    deliver(1);
-    request(1, NB + 1);
+    for (int d = 0; d < NR; ++d) request(d, d);
+    deliver(0, 0);
+    request(0, NR);
+    deliver(1, 1);
+    request(1, NR + 1);
     __syncthreads();
-    for (int t = 0; t < ntiles; t += NB) {
+    for (int t = 0; t < ntiles; t += NR) {
 #pragma unroll
-      for (int d = 0; d < NB; ++d) {
+      for (int d = 0; d < NR; ++d) {
         if (t + d >= ntiles) break;
-        const int set = (d + 2) % NB;
-        deliver(set);
-        request(set, t + d + 2 + NB);
+        const int set = (d + 2) % NR;
+        deliver(set, (d + 2) % NB);
+        request(set, t + d + 2 + NR);
         __syncthreads();
       }
     }
@@ -656,38 +689,44 @@ __device__ __forceinline__ void wide_tile_roles(const GemmParamsT<float>& p, int
   // the hh products and the five small ones in accumulators of their own: the
   // chain of dependent matrix instructions is shorter, and the sum of hh is
   // rounded once for 16 k
+  const Biases<TN, EPI> bias(p, n0, wn, lane);
   floatx16 acc[TM][TN], small[TM][TN];
   clear(acc);
   clear(small);
   const int fa = (lane >> 5) * LA::HALF + (wm + (lane & 31)) * 16;
   const int fb = (lane >> 5) * LB::HALF + (wn + (lane & 31)) * 16 + 3 * LA::PART;
   bf16x8 a[2][TM][3], b[2][TN][3];
-  auto fetch = [&](int set, int buf) {
+  auto fetch = [&](int set, int buf, int s) {
+    const char* const la0 = lds + buf * STAGE + fa + 2 * s * LA::HALF;
+    const char* const lb0 = lds + buf * STAGE + fb + 2 * s * LB::HALF;
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i) a[set][i][q] = fragment(lds + buf * STAGE + fa + i * 512 + q * LA::PART);
+      for (int i = 0; i < TM; ++i) a[set][i][q] = fragment(la0 + i * 512 + q * LA::PART);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) b[set][j][q] = fragment(lds + buf * STAGE + fb + j * 512 + q * LB::PART);
+      for (int j = 0; j < TN; ++j) b[set][j][q] = fragment(lb0 + j * 512 + q * LB::PART);
     }
   };
   __syncthreads();
-  fetch(0, 0);
-  for (int t = 0; t < ntiles; t += 2 * NB) {
+  fetch(0, 0, 0);
+  for (int t = 0; t < ntiles; t += NB) {
 #pragma unroll
-    for (int u = 0; u < 2 * NB; ++u) {
+    for (int u = 0; u < NB; ++u) {
       if (t + u >= ntiles) break;
-      // the next stage's operands are read while this one's are multiplied
-      fetch((u + 1) & 1, (u + 1) % NB);
 #pragma unroll
-      for (int x = 0; x < 6; ++x)
+      for (int s = 0; s < KS; ++s) {
+        // the next 16 k's operands are read while these are multiplied
+        fetch((s + 1) & 1, s + 1 < KS ? u : (u + 1) % NB, (s + 1) % KS);
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int x = 0; x < 6; ++x)
 #pragma unroll
-          for (int j = 0; j < TN; ++j) {
-            floatx16& c = x == 5 ? acc[i][j] : small[i][j];
-            c = NF_MMA(a[u & 1][i][PART_A[x]], b[u & 1][j][PART_B[x]], c);
-          }
+          for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+              floatx16& c = x == 5 ? acc[i][j] : small[i][j];
+              c = NF_MMA(a[s & 1][i][PART_A[x]], b[s & 1][j][PART_B[x]], c);
+            }
+      }
       __syncthreads();
     }
   }
@@ -699,49 +738,78 @@ __device__ __forceinline__ void wide_tile_roles(const GemmParamsT<float>& p, int
   if constexpr (DW) {
     if (by == 0) __syncthreads();
   }
-  wide_epilogue<BM, TM, TN, EPI>(p, acc, m0, n0, wm, wn, lane, bz);
+  wide_epilogue<BM, TM, TN, EPI>(p, acc, bias, m0, n0, wm, wn, lane, bz);
 }
 
 // How a tile is worked on: waves that load and multiply, with or without the
 // second set of fragments, or loading waves of their own.
 enum WideForm { WIDE_PLAIN, WIDE_AHEAD, WIDE_ROLES };
 
+// The problems of a launch: several in the tendencies, one elsewhere (a small
+// launch waits for its arguments).
+template <int EPI>
+struct WideArgs {
+  static constexpr bool DW = EPI == EPI_DW_PARTIAL || EPI == EPI_DW_SGD;
+  static constexpr int MAX = DW ? GEMM_GROUP_MAX : 1;
+  int total, per, n;
+  int start[MAX + 1];                      // first workgroup of each problem
+  GemmParamsT<float> p[MAX];
+};
+
 // Workgroup b runs on XCD b mod 8.  An XCD takes consecutive tiles (the grid
 // is padded to 8 runs of `per`), in bands of 8 tile rows, so that the tiles
-// it works on at one time share their operands in its L2.
+// it works on at one time share their operands in its L2.  (No division where
+// there is one tile row and one piece: the chain of five cost a small launch
+// about as much as its products.)
 template <int BM, int BN, int WM, int WN, int FORM, bool AKC, bool BKC, bool AV, bool BV, int EPI>
-__global__ void __launch_bounds__((BM / WM) * (BN / WN) * (FORM == WIDE_ROLES ? 128 : 64))
-wide_kernel(const GemmGroupT<float> g, int total, int per) {
-  __shared__ __attribute__((aligned(16))) char lds[wide_lds(BM, BN, WIDE_KI, FORM == WIDE_ROLES ? 3 : 2)];
-  const int b = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
-  if (b >= total) return;
+__global__ void __launch_bounds__((BM / WM) * (BN / WN) * (FORM == WIDE_ROLES ? 192 : 64), FORM == WIDE_ROLES ? 6 : 1)
+wide_kernel(const WideArgs<EPI> g) {
+  __shared__ __attribute__((aligned(16))) char lds[FORM == WIDE_ROLES ? wide_lds(BM, BN, WIDE_ROLES_BK, 3)
+                                                                : wide_lds(BM, BN, WIDE_KI, 2)];
+  const int b = (blockIdx.x & 7) * g.per + (blockIdx.x >> 3);
+  if (b >= g.total) return;
   int q = 0;
-  if constexpr (EPI == EPI_DW_PARTIAL || EPI == EPI_DW_SGD) {
+  if constexpr (WideArgs<EPI>::DW) {
 #pragma unroll
     for (int i = 1; i < GEMM_GROUP_MAX; ++i) q += (i < g.n && b >= g.start[i]);
   }
   const GemmParamsT<float>& p = g.p[q];
-  const int r = b - g.start[q];
+  int r = b - (WideArgs<EPI>::DW ? g.start[q] : 0), bz = 0;
   const int mt = (p.M + BM - 1) / BM, nt = (p.N + BN - 1) / BN;
-  const int z = r / (mt * nt), rem = r % (mt * nt);
-  const int band = rem / (8 * nt), inb = rem % (8 * nt);
-  const int bh = min(8, mt - band * 8);
-  const int bx = band * 8 + inb % bh, by = inb / bh, bz = __builtin_amdgcn_readfirstlane(z);
+  if constexpr (EPI == EPI_DW_PARTIAL || EPI == EPI_FWD_PIECE || EPI == EPI_BWD_PIECE) {
+    bz = r / (mt * nt);
+    r -= bz * (mt * nt);
+    bz = __builtin_amdgcn_readfirstlane(bz);
+  }
+  int bx = 0, by = r;
+  if (mt > 1) {
+    const int band = mt > 8 ? r / (8 * nt) : 0;
+    const int inb = r - band * (8 * nt), bh = min(8, mt - band * 8);
+    by = inb / bh;
+    bx = band * 8 + inb - by * bh;
+  }
   if constexpr (FORM == WIDE_ROLES)
-    wide_tile_roles<BM, BN, WM, WN, (BM / WM) * (BN / WN), AKC, BKC, AV, BV, EPI>(p, bx, by, bz, lds);
+    wide_tile_roles<BM, BN, WM, WN, 2 * (BM / WM) * (BN / WN), AKC, BKC, AV, BV, EPI>(p, bx, by, bz, lds);
   else
     wide_tile<BM, BN, WM, WN, FORM == WIDE_AHEAD, AKC, BKC, AV, BV, EPI>(p, bx, by, bz, lds);
 }
 
 template <int BM, int BN, int WM, int WN, int FORM, bool AKC, bool BKC, bool AV, bool BV, int EPI>
-static hipError_t launch_one(GemmGroupT<float> g, const int* nsplit, hipStream_t s) {
-  g.start[0] = 0;
-  for (int q = 0; q < g.n; ++q)
-    g.start[q + 1] = g.start[q] + ((g.p[q].M + BM - 1) / BM) * ((g.p[q].N + BN - 1) / BN) * nsplit[q];
-  for (int q = g.n + 1; q <= GEMM_GROUP_MAX; ++q) g.start[q] = g.start[g.n];
-  const int total = g.start[g.n], per = (total + 7) / 8;
-  return launch_k(wide_kernel<BM, BN, WM, WN, FORM, AKC, BKC, AV, BV, EPI>, dim3(8 * per),
-                  (BM / WM) * (BN / WN) * (FORM == WIDE_ROLES ? 128 : 64), 0, s, g, total, per);
+static hipError_t launch_one(const GemmGroupT<float>& g, const int* nsplit, hipStream_t s) {
+  WideArgs<EPI> a;
+  constexpr int MAX = WideArgs<EPI>::MAX;
+  a.n = g.n;
+  a.start[0] = 0;
+  for (int q = 0; q < MAX; ++q) {
+    a.p[q] = g.p[q];
+    a.start[q + 1] = a.start[q];
+    if (q < g.n)
+      a.start[q + 1] += ((g.p[q].M + BM - 1) / BM) * ((g.p[q].N + BN - 1) / BN) * nsplit[q];
+  }
+  a.total = a.start[MAX];
+  a.per = (a.total + 7) / 8;
+  return launch_k(wide_kernel<BM, BN, WM, WN, FORM, AKC, BKC, AV, BV, EPI>, dim3(8 * a.per),
+                  (BM / WM) * (BN / WN) * (FORM == WIDE_ROLES ? 192 : 64), 0, s, a);
 }
 
 template <int BM, int BN, int WM, int WN, int FORM>

@@ -17,6 +17,13 @@ EDGES = [
     ((129, 193, 66), ("tanh", "sigmoid"), 1, 1, 0.5, "64x64"),        # one row; aligned and not
     ((17, 130, 65, 3), ("sigmoid", "tanh", "sigmoid"), 63, 1, 0.5, "64x64"),
     ((1001, 200, 131), ("tanh", "sigmoid"), 191, 1, 0.5, "64x64"),    # k = 1001: partial last stage
+    # k and rows about the stages of 32 and the 8 rows that share a branch
+    ((16, 133, 31), ("sigmoid", "tanh"), 7, 1, 0.5, "64x64"),
+    ((32, 160, 1), ("gaussian", "sigmoid"), 8, 1, 0.5, "64x64"),
+    ((33, 129, 47), ("tanh",), 9, 3, 0.5, "64x64"),
+    ((48, 224, 64), ("sigmoid",), 33, 1, 0.5, "64x64"),
+    ((95, 193, 65), ("tanh", "gaussian"), 65, 1, 0.2, "64x64"),
+    ((97, 131, 7), ("relu", "sigmoid"), 40, 2, 0.2, "64x64"),
     ((515, 1023, 1030), ("gaussian", "sigmoid"), 4095, 1, 0.2, "128x128"),
     ((512, 1024, 1153), ("tanh", "sigmoid"), 3969, 3, 0.2, "128x128"),
     ((31, 4093, 4090), ("tanh", "sigmoid"), 4081, 1, 0.02, "256x256"),
