@@ -520,10 +520,13 @@ __device__ __forceinline__ void wide_tile(const GemmParamsT<float>& p, int bx, i
     for (int q = 0; q < 3; ++q) a[set][i][q] = fragment(buf + fa + i * 512 + q * LA::PART);
   };
   // the order of a stage's instructions: matrix instructions with the LDS
-  // accesses and a share of the vector instructions between them
+  // accesses and a share of the vector instructions between them.  In the 128 x 128
+  // tile (FD) the shares are the ones that measured best: forward 10000 x 784-1024^3
+  // 409 us at 6, 397 at 5 and 4, 408 at 9; the tendencies of 4096 samples 203 at 6, 196 at
+  // 8, 188 at 11, 193 at 16.
   constexpr int NM = 6 * TM * TN, NR = 3 * (TM + TN);
   constexpr int NV = 26 * (LA::Q + LB::Q) + (DW ? 4 * LA::Q : 0) + 16;
-  constexpr int VPM = (NV + NM - 1) / NM;
+  constexpr int VPM = FD ? (DW ? 11 : 5) : (NV + NM - 1) / NM;
   // FD: stage t's operands are in fragment set t & 1, stage t + 1 in LDS
   // buffer (t + 1) & 1, stages t + 2 and t + 3 in the register sets (stage s
   // in set s & 1).  Otherwise stage t is in LDS buffer t & 1, stages t + 1
