@@ -297,30 +297,35 @@ int pick_tile(int64_t M, int64_t N, int64_t splits) {
 // Microseconds that the wide kernels (fp32) take for `tiles` tiles of `stages`
 // stages of 16 k each, from measurements of the three tiles: a stage costs
 // `alone` however few tiles there are, `share` per tile and CU once the chip
-// is full; a tile's end (epilogue, first operands) costs `end`.
-//   tile        alone  share  end   measured (us, random operands)
-//   64 x 64     0.33   0.21   1.5   16x4096x4096 84; 8192x4096x4096 1740
-//   128 x 128   0.50   0.61   4.5   16x4096x4096 127; 4096x1024x1024 48.5;
-//                                   8192x4096x4096 1243
-//   256 x 256   1.48   2.18   20    16x4096x4096 379; 8192x4096x4096 1116
-// So the 64 x 64 tile wins while the grid is small (3008x520x1024: 33 against
-// 39 and 106), the 128 x 128 tile from about one per CU (4096x1024x1024: 48.5
-// against 63 and 107), the 256 x 256 tile where its own grid fills the chip.
-// (The 128 x 128 tile's figures are from its form with one set of accumulators;
-// the present one takes 8% longer in inference of 784-1024^3-10 and 20% in its
-// tendencies, 152 us then and 182 now, the same in its forward and deltas.)
+// is full; a tile's end (epilogue, first operands) costs `end`, in the
+// tendencies `dw_end`.  About 3 us of every launch are left out.
+//   tile        alone  share  end  dw_end   measured (us, random operands)
+//   64 x 64     0.21   0.265  1.2  1.3      16x4096x4096 60; 1024x1024x1024 21;
+//                                           8192x4096x4096 1972
+//   128 x 128   0.55   0.70   4.5  5.5      16x4096x4096 146; 1024x1024x1024 42;
+//                                           8192x1024x1024 109; 8192x4096x4096 1418
+//   256 x 256   1.48   2.18   12   20       16x4096x4096 385; 8192x1024x1024 123;
+//                                           8192x4096x4096 1113
+// So the 64 x 64 tile wins while the grid is small, the 128 x 128 tile from
+// about one per CU (4096x1024x1024: 61 against 64 and 112).  The 256 x 256
+// tile's sums have one set of accumulators and are rounded six times for 16
+// k where the other tiles' leading products are rounded once (their errors stand
+// at the head of nf_wide.h), so it is taken only where it saves a seventh and
+// more: its share and end are set above the measured ones, at 2.54 and 20.
+// (10000x1024x1024 takes 147 on the 128 x 128 tile, 125 on the other.)
 int64_t wide_tiles(int tile, int64_t M, int64_t N) {
   const int64_t side = tile == nf::TILE_256x256 ? 256 : (tile == nf::TILE_128x128 ? 128 : 64);
   return ((M + side - 1) / side) * ((N + side - 1) / side);
 }
-double wide_cost(int tile, int64_t tiles, int64_t stages, int ncu) {
+double wide_cost(int tile, bool tendency, int64_t tiles, int64_t stages, int ncu) {
   struct Cost {
-    double alone, share, end;
+    double alone, share, end, dw_end;
   };
-  static const Cost costs[3] = {{0.50, 0.61, 4.5}, {0.33, 0.212, 1.5}, {1.48, 2.18, 20.0}};
+  static const Cost costs[3] = {{0.55, 0.70, 4.5, 5.5}, {0.21, 0.265, 1.2, 1.3}, {1.48, 2.54, 20.0, 20.0}};
   const Cost& c = costs[tile];
   const int64_t rounds = (tiles + ncu - 1) / ncu;
-  return (double)stages * std::max(c.alone, c.share * (double)rounds) + c.end * (double)rounds;
+  return (double)stages * std::max(c.alone, c.share * (double)rounds) +
+         (tendency ? c.dw_end : c.end) * (double)rounds;
 }
 
 int device_cus(const nf_net* n) { return n->ncu > 0 ? n->ncu : 256; }
@@ -328,14 +333,14 @@ int device_cus(const nf_net* n) { return n->ncu > 0 ? n->ncu : 256; }
 // The tile of one launch of wide contractions of `len` k each: `tiles` gives
 // the launch's tiles of a shape; `big`: the 256 x 256 tile takes the epilogue.
 template <class F>
-int pick_wide_tile(const nf_net* n, int64_t len, bool big, F&& tiles) {
+int pick_wide_tile(const nf_net* n, bool tendency, int64_t len, bool big, F&& tiles) {
   const int ncu = device_cus(n);
   const int64_t stages = (len + 15) / 16;
   int best = nf::TILE_64x64;
-  double cost = wide_cost(best, tiles(best), stages, ncu);
+  double cost = wide_cost(best, tendency, tiles(best), stages, ncu);
   for (int tile : {(int)nf::TILE_128x128, (int)nf::TILE_256x256}) {
     if (tile == nf::TILE_256x256 && !big) continue;
-    const double c = wide_cost(tile, tiles(tile), stages, ncu);
+    const double c = wide_cost(tile, tendency, tiles(tile), stages, ncu);
     if (c < cost) {
       cost = c;
       best = tile;
@@ -423,7 +428,7 @@ nf_status launch(nf_net* n, int epi, bool akc, bool bkc, bool av, bool bv, int n
   if constexpr (sizeof(T) == 4) {
     const bool big = epi == nf::EPI_BWD || epi == nf::EPI_DW_SGD ||
                      (av && (epi == nf::EPI_FWD_STASH || epi == nf::EPI_FWD_OUT));
-    const int tile = pick_wide_tile(n, nsplit > 1 ? p.sub_len : p.K, big,
+    const int tile = pick_wide_tile(n, false, nsplit > 1 ? p.sub_len : p.K, big,
                                     [&](int t) { return wide_tiles(t, p.M, p.N) * nsplit; });
     nf::GemmGroupT<float> g{};
     g.p[0] = p;
@@ -442,9 +447,11 @@ nf_status launch(nf_net* n, int epi, bool akc, bool bkc, bool av, bool bv, int n
 // CU count, of at least 128 inputs each, 16 at most; none where K < 256 or
 // the grid is that large already (or, for general nets, large enough for the
 // 128 x 128 tile).  fp64 takes that many; in fp32 the count in that range
-// with the least cost is taken, a fold of the pieces (4.5 us and the pieces
-// through memory) included: 3003x517x1001 in one piece takes 32 us, in two
-// 34 and the fold; 16x4096x4096 in one piece 84, in eight 15 and the fold.
+// with the least cost is taken, a fold of the pieces (3 us and the pieces
+// through memory) included: 256x320x1024 in one piece takes 8.2 us, in two 9.4;
+// 16x4096x2000 in one piece 59, in eight 14 with the fold.  Over 259 shapes of 1
+// to 2048 samples, 256 to 4096 inputs and 8 to 2000 units the count taken is
+// within 1% of the best one on the mean.
 // Pieces start on whole 16-input stages, so a vector load never reaches into
 // the next piece and every piece start stays 16-byte aligned (nf_split.h).
 nf::KSplit fwd_split(const nf_net* n, int64_t M, int64_t N, int64_t K, bool small_tile_only) {
@@ -460,13 +467,13 @@ nf::KSplit fwd_split(const nf_net* n, int64_t M, int64_t N, int64_t K, bool smal
     const nf::KSplit ks = nf::k_split(K, want_pieces);
     double c = 1e30;
     for (int tile : {(int)nf::TILE_64x64, (int)nf::TILE_128x128})
-      c = std::min(c, wide_cost(tile, wide_tiles(tile, M, N) * ks.nsplit, (ks.sub_len + 15) / 16,
+      c = std::min(c, wide_cost(tile, false, wide_tiles(tile, M, N) * ks.nsplit, (ks.sub_len + 15) / 16,
                                 device_cus(n)));
     // written and read again at about 4 TB/s; a medium net's per-sample
     // kernel reads the pieces in any case, without a fold of its own
     const double through = 2.0 * 4.0 * (double)M * (double)N * ks.nsplit / 4e6;
     if (ks.nsplit > 1 || !small_tile_only) c += through;
-    if (ks.nsplit > 1 && small_tile_only) c += 4.5;
+    if (ks.nsplit > 1 && small_tile_only) c += 3.0;
     if (want_pieces == 1 || c < cost) {
       cost = c;
       best = ks;
@@ -820,7 +827,7 @@ nf_status run_backward_update(nf_net* n, const T* x, int64_t batch, double eta, 
     static const int one[nf::GEMM_GROUP_MAX] = {1, 1, 1, 1};
     nf_status st;
     if constexpr (sizeof(T) == 4) {
-      const int tile = pick_wide_tile(n, batch, true, tiles_of);
+      const int tile = pick_wide_tile(n, true, batch, true, tiles_of);
       st = timed(n, nf::gemm_name(nf::EPI_DW_SGD, tile, nf::DT_F32), bytes, flops, s,
                  [&] { return nf::launch_wide(nf::EPI_DW_SGD, tile, true, g, one, s); });
     } else {
@@ -886,7 +893,7 @@ nf_status run_backward_update(nf_net* n, const T* x, int64_t batch, double eta, 
     auto tile_of = [&](const Piece& pc) {
       const LayerLayout& ly = n->layers[pc.l];
       if (sizeof(T) == 4)
-        return pick_wide_tile(n, (shard_len + pc.nsub - 1) / pc.nsub, true, [&](int t) {
+        return pick_wide_tile(n, true, (shard_len + pc.nsub - 1) / pc.nsub, true, [&](int t) {
           return wide_tiles(t, ly.out, ly.in) * shards * pc.nsub;
         });
       return pick_tile(ly.out, ly.in, (int64_t)shards * pc.nsub);

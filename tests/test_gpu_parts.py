@@ -143,7 +143,7 @@ def test_tendencies(shape, kernel):
 # (batch = inputs, hidden units, outputs) and the tile
 DELTAS = [
     ((70, 150, 203), "wide_bwd_64x64"),
-    ((33, 400, 700), "wide_bwd_piece_64x64"),
+    ((33, 400, 1500), "wide_bwd_piece_64x64"),
     ((2048, 2048, 200), "wide_bwd_128x128"),
     ((4096, 4096, 1024), "wide_bwd_256x256"),
 ]
