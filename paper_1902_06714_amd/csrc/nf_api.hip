@@ -986,6 +986,17 @@ nf::NarrowFwdParamsT<T> narrow_fwd_params(const nf_net* n, const T* x, const T* 
   p.Y = y;
   p.B = (int)batch;
   p.d0 = n->dims[0];
+// The training step of odd fp32 rows takes the narrow kernels up to this many
+// samples: their tendencies go through the whole batch in each workgroup, where the
+// medium path splits it (us a step, narrow and medium: 785-30-10 at 3000 samples 22.4
+// and 27.2, 5000 36.9 and 28.5; 5-26-16 22.0 and 21.2, 16000 84.9 and 29.9;
+// 1027-12-10 28.0 and 25.2).
+constexpr int64_t NARROW_ODD_BATCH = 3000;
+template <class T>
+bool narrow_step_ok(const nf_net* n, const T* x, int64_t batch, int shards) {
+  return shards == 1 && narrow_rows_ok<T>(n, x) && (vec_ok(x, n->dims[0]) || batch <= NARROW_ODD_BATCH);
+}
+
   p.L = L;
   p.dims[0] = n->dims[0];
   for (int l = 1; l <= nf::NARROW_MAX_LAYERS; ++l) {
@@ -1238,7 +1249,7 @@ template <class T>
 nf_status train_step(nf_net* n, const T* x, const T* y, int64_t batch, double eta, int shards,
                      hipStream_t s) {
   nf_status st;
-  const bool narrow = shards == 1 && narrow_rows_ok<T>(n, x);
+  const bool narrow = narrow_step_ok<T>(n, x, batch, shards);
   nf::MediumParamsT<T> mp{};
   if (narrow) {
     st = narrow_train_step<T>(n, x, y, batch, eta, s);
@@ -1655,7 +1666,7 @@ nf_status train_batch(nf_net* net, const T* d_x, const T* d_y, int64_t batch, do
 // backward pass starts) or the tendency pieces, whichever is larger.
 template <class T>
 int64_t partial_need(const nf_net* n, const T* x, int64_t batch, int shards) {
-  if (shards == 1 && narrow_rows_ok<T>(n, x)) return 0;
+  if (narrow_step_ok<T>(n, x, batch, shards)) return 0;
   std::vector<DwPiece> pieces;
   int64_t need = dw_plan(n, batch, shards, &pieces);
   nf::MediumParamsT<T> mp{};

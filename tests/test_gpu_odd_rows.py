@@ -28,6 +28,10 @@ CASES = [
     ((111, 128, 16, 7, 3), ("tanh",), 1000, 4, ("fwd_skinny", "dw_skinny"), "medium_infer"),
     ((2050, 113, 9), ("tanh", "sigmoid"), 515, 5, ("fwd_skinny", "dw_skinny"), "medium_infer"),
     ((784, 100, 30), ("sigmoid",), 6001, 1, ("fwd_skinny", "dw_skinny"), "medium_infer"),
+    # the last batch of the narrow step and the first past it
+    ((29, 26, 16), ("tanh", "sigmoid"), 3000, 1, ("narrow_fwd16_train",), "narrow_fwd16_infer"),
+    ((29, 26, 16), ("tanh", "sigmoid"), 3001, 1, ("fwd_skinny", "dw_skinny"), "narrow_fwd16_infer"),
+    ((29, 26), ("sigmoid",), 3001, 1, ("dw_skinny",), "narrow_fwd16_infer"),
 ]
 
 
