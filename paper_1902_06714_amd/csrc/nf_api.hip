@@ -864,7 +864,13 @@ nf_status run_backward_update(nf_net* n, const T* x, int64_t batch, double eta, 
       for (size_t j = 0; j < pieces.size() && g.n < nf::GEMM_GROUP_MAX; ++j) {
         const Piece& pj = pieces[j];
         const nf::GemmParamsT<T> p = piece_params(pj);
-        // (the fp32 kernel reads input rows of any pitch)
+        // The fp32 kernel reads input rows of any pitch, but those that are not
+        // whole vectors no faster than the wide kernels where there is much of
+        // them (us a step, skinny and wide: 1958-121-80-3 at 7970 samples 148 and 121,
+        // at 2049 57 and 63; 785-120-10 at 10000 68.4 and 68.2; 1957-60-10 70 and 79)
+        if (sizeof(T) == 4 && p.M > 96 && !vec_ok(p.B, p.ldb) &&
+            (double)p.M * (double)p.N * (double)batch > 1e9)
+          continue;
         if (p.M > nf::SKINNY_MAX_UNITS || !vec_ok(p.A, p.lda) ||
             (sizeof(T) == 8 ? !vec_ok(p.B, p.ldb) : (reinterpret_cast<uintptr_t>(p.B) & 3) != 0))
           continue;

@@ -32,6 +32,9 @@ CASES = [
     ((29, 26, 16), ("tanh", "sigmoid"), 3000, 1, ("narrow_fwd16_train",), "narrow_fwd16_infer"),
     ((29, 26, 16), ("tanh", "sigmoid"), 3001, 1, ("fwd_skinny", "dw_skinny"), "narrow_fwd16_infer"),
     ((29, 26), ("sigmoid",), 3001, 1, ("dw_skinny",), "narrow_fwd16_infer"),
+    # much of more than 96 units: the wide tendencies beside the skinny ones
+    ((1961, 97, 5), ("tanh", "sigmoid"), 5265, 5, ("fwd_skinny", "wide_dw_partial_128x128", "dw_skinny"),
+     "medium_infer"),
 ]
 
 
