@@ -846,7 +846,7 @@ nf_status run_backward_update(nf_net* n, const T* x, int64_t batch, double eta, 
 
   // the piece kernels, grouped by tile shape and B-row vector loads (layer
   // order within a group), up to GEMM_GROUP_MAX layers per launch; layers of
-  // at most SKINNY_MAX_UNITS units with 16-byte operand rows take the skinny
+  // at most SKINNY_MAX_UNITS units (in fp64 with 16-byte operand rows) take the skinny
   // tendency kernel of their element type
   const int dtype = dtype_of<T>();
   std::vector<bool> done(pieces.size(), false);
@@ -986,16 +986,6 @@ bool narrow_rows_ok(const nf_net* n, const T* x) {
          (int64_t)n->dims[0] * nf::NARROW_WIDTH * (int64_t)sizeof(T) < (int64_t)nf::NARROW_OOB;
 }
 
-template <class T>
-nf::NarrowFwdParamsT<T> narrow_fwd_params(const nf_net* n, const T* x, const T* y, int64_t batch,
-                                          T* out) {
-  nf::NarrowFwdParamsT<T> p{};
-  const int L = num_layers(n);
-  T* P = cur_params<T>(n);
-  p.X = x;
-  p.Y = y;
-  p.B = (int)batch;
-  p.d0 = n->dims[0];
 // The training step of odd fp32 rows takes the narrow kernels up to this many
 // samples: their tendencies go through the whole batch in each workgroup, where the
 // medium path splits it (us a step, narrow and medium: 785-30-10 at 3000 samples 22.4
@@ -1007,6 +997,16 @@ bool narrow_step_ok(const nf_net* n, const T* x, int64_t batch, int shards) {
   return shards == 1 && narrow_rows_ok<T>(n, x) && (vec_ok(x, n->dims[0]) || batch <= NARROW_ODD_BATCH);
 }
 
+template <class T>
+nf::NarrowFwdParamsT<T> narrow_fwd_params(const nf_net* n, const T* x, const T* y, int64_t batch,
+                                          T* out) {
+  nf::NarrowFwdParamsT<T> p{};
+  const int L = num_layers(n);
+  T* P = cur_params<T>(n);
+  p.X = x;
+  p.Y = y;
+  p.B = (int)batch;
+  p.d0 = n->dims[0];
   p.L = L;
   p.dims[0] = n->dims[0];
   for (int l = 1; l <= nf::NARROW_MAX_LAYERS; ++l) {
@@ -1282,6 +1282,18 @@ nf_status train_step(nf_net* n, const T* x, const T* y, int64_t batch, double et
   return st;
 }
 
+// Medium nets whose inference is faster layer by layer: fp32 nets of two layers, where
+// that saves no launch, on many samples of few inputs (us, medium path and layers: 64-
+// 103-38 at 8192 samples 16.3 and 13.4, 14616 23.7 and 16.5, but 4096 11.8 and 13.3; 784-
+// 100-10 at 10000 27.4 and 32.5; 64-100-100-10 at 10000 21.6 and 24.9) and on the fewest
+// samples of many inputs (1824-120-6, one sample 14.9 and 13.9, 2048 samples
+// 25.6 and 23.3, 3000 26.4 and 28.7; 784-100-10, one sample 13.1 and 13.6).
+template <class T>
+bool infer_by_layer(const nf_net* n, int64_t batch) {
+  return sizeof(T) == 4 && num_layers(n) == 2 &&
+         ((n->dims[0] <= 256 && n->dims[1] > 64 && batch >= 8192) || (n->dims[0] >= 1024 && batch <= 16));
+}
+
 // f(z_L) of `batch` samples into out [batch][d_L] (inference, no stash)
 template <class T>
 nf_status infer(nf_net* n, const T* x, int64_t batch, T* out, hipStream_t s) {
@@ -1304,7 +1316,7 @@ nf_status infer(nf_net* n, const T* x, int64_t batch, T* out, hipStream_t s) {
   // two launches, where a launch a layer and the fold of layer 1's pieces
   // took five for three layers (784-116-46-41-12 at 505 samples: 29.3 us, 18.2)
   nf::MediumParamsT<T> mp{};
-  if (medium_layout<T>(n, batch, &mp))
+  if (!infer_by_layer<T>(n, batch) && medium_layout<T>(n, batch, &mp))
     return medium_forward_deltas<T>(n, x, nullptr, batch, out, s);
   return run_forward<T>(n, x, nullptr, batch, out, false, s);
 }

@@ -35,6 +35,11 @@ CASES = [
     # much of more than 96 units: the wide tendencies beside the skinny ones
     ((1961, 97, 5), ("tanh", "sigmoid"), 5265, 5, ("fwd_skinny", "wide_dw_partial_128x128", "dw_skinny"),
      "medium_infer"),
+    # inference layer by layer
+    ((255, 65, 3), ("tanh", "sigmoid"), 8192, 1, ("fwd_skinny",), "wide_fwd_out_64x64"),
+    ((255, 64, 3), ("tanh", "sigmoid"), 8192, 1, ("fwd_skinny",), "medium_infer"),
+    ((1025, 40, 3), ("tanh", "sigmoid"), 16, 1, ("fwd_skinny",), "wide_fwd_out_64x64"),
+    ((1025, 40, 3), ("tanh", "sigmoid"), 17, 1, ("fwd_skinny",), "medium_infer"),
 ]
 
 
