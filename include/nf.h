@@ -30,6 +30,12 @@
  *   net is unchanged, and nf_last_error() gives a message for this thread.
  *   No C++ exception crosses the ABI.
  * - A net is not thread-safe: calls on one net must not overlap.
+ * - Parameters and tendencies pass between host and device through pinned host
+ *   memory that the nets of a device share: at most 8 MiB, allocated by the
+ *   first calls that need it (set, get, save, load) and given back with the
+ *   last net.  Such a call on more than 1 MiB starts up to seven host threads,
+ *   which end with it; calls on different nets at one time divide the memory
+ *   and may wait for one another.
  */
 #ifndef NF_H
 #define NF_H

@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <condition_variable>
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
@@ -121,12 +122,6 @@ struct nf_net {
   void* w1pack = nullptr;
   int64_t w1f_elems = 0;
   uint64_t pver = 1, packver = 0;
-  // pinned host memory that parameters and tendencies pass through: slots of
-  // slot_bytes each; null when it could not be had (they are then copied
-  // matrix by matrix)
-  void* staging = nullptr;
-  int64_t slot_bytes = 0;
-  int slots = 0;
   // medium nets: layer 1's plan for the last batch size (a plan takes about a
   // microsecond to make, a small step's launches five)
   int64_t skinny_batch = 0;
@@ -175,8 +170,7 @@ nf_status sync_net(nf_net* n) {
   return NF_OK;
 }
 
-// the parameter buffers, the tendencies, the packed copies of W_1 and the
-// staging memory
+// the parameter buffers, the tendencies and the packed copies of W_1
 void free_params(nf_net* n) {
   for (void*& b : n->pbuf) {
     if (b) (void)hipFree(b);
@@ -184,10 +178,8 @@ void free_params(nf_net* n) {
   }
   if (n->grads) (void)hipFree(n->grads);
   if (n->w1pack) (void)hipFree(n->w1pack);
-  if (n->staging) (void)hipHostFree(n->staging);
   n->grads = nullptr;
   n->w1pack = nullptr;
-  n->staging = nullptr;
 }
 
 void free_ws(nf_net* n) {
@@ -1373,6 +1365,79 @@ nf_status guarded(F&& f) {
 // 1024^3-10, 11.7 MB: 0.81, 0.36, 0.38).
 constexpr int64_t kSlotBytes = 1 << 20;
 constexpr int kSlots = 8;
+constexpr int kMaxDevices = 64;
+
+// The slots of a device are its nets': allocated as calls first need them (about
+// 0.3 ms an allocation, where creating a net takes 0.02) and given back with
+// the last net.
+struct SlotPool {
+  std::mutex mu;
+  std::condition_variable returned;
+  int nets = 0;
+  int made = 0, idle = 0, blocks = 0;
+  char* slot[kSlots];              // the idle ones
+  void* block[kSlots];             // allocations
+};
+SlotPool& slot_pool(int dev) {
+  // never destroyed: a net may outlive the statics of its program
+  static SlotPool* const pools = new SlotPool[kMaxDevices];
+  return pools[dev];
+}
+
+void join_slots(int dev) {
+  if (dev >= kMaxDevices) return;
+  SlotPool& p = slot_pool(dev);
+  std::lock_guard<std::mutex> lock(p.mu);
+  ++p.nets;
+}
+
+void leave_slots(int dev) {
+  if (dev >= kMaxDevices) return;
+  SlotPool& p = slot_pool(dev);
+  std::lock_guard<std::mutex> lock(p.mu);
+  if (--p.nets > 0) return;
+  for (int i = 0; i < p.blocks; ++i) (void)hipHostFree(p.block[i]);
+  p.made = p.idle = p.blocks = 0;
+}
+
+// Up to `want` slots of the current device `dev` for one call, one at least
+// unless there is no pinned memory to be had (count 0).  A call that finds
+// none idle waits for another thread's to be returned; it holds none itself
+// while it waits.
+struct Slots {
+  SlotPool* pool = nullptr;
+  char* slot[kSlots];
+  int count = 0;
+  Slots(int dev, int want) {
+    if (dev >= kMaxDevices) return;
+    pool = &slot_pool(dev);
+    std::unique_lock<std::mutex> lock(pool->mu);
+    const int more = std::min(want - pool->idle, kSlots - pool->made);
+    if (more > 0) {
+      void* b = nullptr;
+      if (hipHostMalloc(&b, (size_t)(kSlotBytes * more), hipHostMallocDefault) == hipSuccess) {
+        pool->block[pool->blocks++] = b;
+        for (int i = 0; i < more; ++i) pool->slot[pool->idle++] = static_cast<char*>(b) + i * kSlotBytes;
+        pool->made += more;
+      } else {
+        (void)hipGetLastError();
+      }
+    }
+    if (pool->made == 0) return;
+    pool->returned.wait(lock, [&] { return pool->idle > 0; });
+    while (count < want && pool->idle > 0) slot[count++] = pool->slot[--pool->idle];
+  }
+  ~Slots() {
+    if (count == 0) return;
+    {
+      std::lock_guard<std::mutex> lock(pool->mu);
+      while (count > 0) pool->slot[pool->idle++] = slot[--count];
+    }
+    pool->returned.notify_all();
+  }
+  Slots(const Slots&) = delete;
+  Slots& operator=(const Slots&) = delete;
+};
 
 nf_status create(const int32_t* dims, int32_t n_dims, const int32_t* acts, int32_t n_acts,
                  int32_t dtype, nf_net** out) {
@@ -1458,13 +1523,7 @@ nf_status create(const int32_t* dims, int32_t n_dims, const int32_t* acts, int32
     return fail(e == hipErrorOutOfMemory ? NF_ENOMEM : NF_EDEVICE,
                 std::string("device allocation failed: ") + hipGetErrorString(e));
   }
-  const int64_t pbytes = round_up(n->n_params * (int64_t)n->esz, 16);
-  n->slot_bytes = std::min(pbytes, kSlotBytes);
-  n->slots = (int)std::min<int64_t>(kSlots, (pbytes + n->slot_bytes - 1) / n->slot_bytes);
-  if (hipHostMalloc(&n->staging, (size_t)(n->slot_bytes * n->slots), hipHostMallocDefault) != hipSuccess) {
-    (void)hipGetLastError();
-    n->staging = nullptr;
-  }
+  join_slots(n->device);
   *out = n;
   return NF_OK;
 }
@@ -1513,13 +1572,13 @@ hipError_t move_canonical(const nf_net* n, bool to_buf, T* buf, T* dev, int64_t 
 
 // All canonical elements through the slots, slot t's by thread t.
 template <class T>
-hipError_t stage_params(const nf_net* n, T* dev, const T* host_src, T* host_dst) {
-  const int64_t per = n->slot_bytes / (int64_t)sizeof(T);
+hipError_t stage_params(const nf_net* n, const Slots& slots, T* dev, const T* host_src, T* host_dst) {
+  const int64_t per = kSlotBytes / (int64_t)sizeof(T);
   const int64_t chunks = (n->n_params + per - 1) / per;
-  const int workers = (int)std::min<int64_t>(n->slots, chunks);
+  const int workers = slots.count;
   std::atomic<int> failed{(int)hipSuccess};
   auto work = [&](int t) {
-    T* buf = reinterpret_cast<T*>(static_cast<char*>(n->staging) + t * n->slot_bytes);
+    T* buf = reinterpret_cast<T*>(slots.slot[t]);
     hipEvent_t ev = nullptr;
     hipError_t e = hipSetDevice(n->device);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
@@ -1559,13 +1618,15 @@ nf_status copy_params(nf_net* n, void* dev, const void* host_src, void* host_dst
   if (st != NF_OK) return st;
   if (host_src) ++n->pver;   // the packed copies of W_1 no longer match
   const size_t es = n->esz;
-  if (n->staging) {
+  const int64_t chunks = (n->n_params * (int64_t)es + kSlotBytes - 1) / kSlotBytes;
+  const Slots slots(n->device, (int)std::min<int64_t>(kSlots, chunks));
+  if (slots.count > 0) {
     const hipError_t e =
         n->dtype == nf::DT_F64
-            ? stage_params<double>(n, static_cast<double*>(dev), static_cast<const double*>(host_src),
-                                   static_cast<double*>(host_dst))
-            : stage_params<float>(n, static_cast<float*>(dev), static_cast<const float*>(host_src),
-                                  static_cast<float*>(host_dst));
+            ? stage_params<double>(n, slots, static_cast<double*>(dev),
+                                   static_cast<const double*>(host_src), static_cast<double*>(host_dst))
+            : stage_params<float>(n, slots, static_cast<float*>(dev),
+                                  static_cast<const float*>(host_src), static_cast<float*>(host_dst));
     if (e != hipSuccess) return hip_fail(e, "parameter copy");
     return NF_OK;
   }
@@ -1730,7 +1791,6 @@ static __device__ __align__(256) unsigned char scratch[NF_NOALLOC_SCRATCH_BYTES]
 
 namespace {
 
-constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_addr[kMaxDevices] = {};
 
@@ -2112,6 +2172,7 @@ nf_status nf_net_destroy(nf_net* net) {
     if (net->evalbuf) (void)hipFree(net->evalbuf);
     if (net->dcount) (void)hipFree(net->dcount);
     free_params(net);
+    leave_slots(net->device);
     delete net;
     return st;
   });

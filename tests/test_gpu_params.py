@@ -35,3 +35,33 @@ def test_round_trip(dims, f64):
             assert np.array_equal(get(net), scale * theta)
     finally:
         nf.nf_net_destroy(net)
+
+
+def test_shared_slots():
+    """Nets share the slots: several threads at a time, more of them than slots,
+    and nets that come after the last one has given them back."""
+    import threading
+    from paper_1902_06714_amd import nf
+    wrong = []
+
+    def work(k):
+        dims = [(1023, 1025, 7), (33, 5), (2049, 513, 2), (700, 700)][k % 4]
+        net = nf.nf_net_create(dims, "sigmoid")
+        try:
+            n = nf.nf_param_count(net)
+            theta = np.random.default_rng(k).normal(size=n).astype(np.float32)
+            for i in range(6):
+                nf.nf_set_params(net, theta + np.float32(i))
+                if not np.array_equal(nf.nf_get_params(net), theta + np.float32(i)):
+                    wrong.append((k, i))
+        finally:
+            nf.nf_net_destroy(net)
+
+    for rounds in range(3):
+        note(f"shared slots, round {rounds}")
+        threads = [threading.Thread(target=work, args=(k,)) for k in range(12)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+    assert not wrong
