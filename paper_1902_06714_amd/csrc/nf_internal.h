@@ -154,10 +154,11 @@ hipError_t launch_wide(int epi, int tile, bool a_vec, const GemmGroupT<float>& g
 
 // The tendency pieces of up to GEMM_GROUP_MAX fp32 layers of at most
 // SKINNY_MAX_UNITS units in one launch, operands loaded straight into the
-// matrix cores (csrc/nf_skinny.hip); same piece layout as
-// launch_dw_partial_group.  Problem q has npieces[q] pieces; start[] is
-// filled by the launcher.  Both operands and the piece buffer need 16-byte
-// aligned rows with pitches of whole 16-byte vectors.
+// matrix cores (csrc/nf_skinny.hip); same piece layout as launch_wide's
+// EPI_DW_PARTIAL.  Problem q has npieces[q] pieces; start[] is filled by the
+// launcher.  A (the deltas) and the piece buffer need 16-byte aligned rows with
+// pitches of whole 16-byte vectors; B (the inputs) any pitch, at any 4-byte
+// address.
 constexpr int SKINNY_MAX_UNITS = 128;
 constexpr int SKINNY_PD = 4;    // k-steps of operand loads in flight
 struct SkinnyGroup {

@@ -24,15 +24,11 @@ namespace nf {
 
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
-// The matrix-core instruction of each element type, as the contraction uses
-// it: a BLK x BLK block of C per instruction, KS values of k per instruction.
+// The fp64 matrix-core instruction as the contraction uses it: a BLK x BLK
+// block of C per instruction, KS values of k per instruction.
 // Lane l supplies A(a_row(l), k0 + k_of(l)) and B(k0 + k_of(l), a_row(l)), and
 // accumulator register v of lane l holds C(row(v, l), col(l)) of the block.
-template <class T>
-struct Mma;
-
-template <>
-struct Mma<double> {
+struct MM {
   static constexpr int BLK = 16, KS = 4, NACC = 4;
   typedef doublex4 acc_t;
   __device__ static __forceinline__ acc_t mma(double a, double b, acc_t c) {
@@ -69,6 +65,7 @@ struct alignas(16) Vec16 {
 // every load is unconditional, stages past the end included.
 template <class T, int R, int BK, int NT, bool KC, bool VEC>
 struct TileLoader {
+  static_assert(sizeof(T) == 8, "single values are read 8 bytes at a time");
   static constexpr int VW = Vec16<T>::N;
   static constexpr int SR = R + (KC ? 2 : 4);
   static constexpr int NV = VEC ? (R * BK / VW) / NT : (R * BK) / NT;
@@ -114,10 +111,7 @@ struct TileLoader {
         const int gr = r0 + r, gk = k0 + k;
         const int e = KC ? r * ldi + gk : k * ldi + gr;
         const unsigned off = (gr < rmax && gk < kend) ? (unsigned)e * (unsigned)sizeof(T) : TILE_OOB;
-        if constexpr (sizeof(T) == 4)
-          s[i] = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
-        else
-          s[i] = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0));
+        s[i] = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0));
       }
     }
   }
@@ -160,7 +154,6 @@ struct TileLoader {
 template <class T, int BM, int BN, int BK, int WM, int WN, int PD, bool AKC, bool BKC, bool AV,
           bool BV, int EPI>
 __device__ __forceinline__ void gemm_tile(const GemmParamsT<T>& p, int bx, int by, int bz) {
-  using MM = Mma<T>;
   constexpr int NT = (BM / WM) * (BN / WN) * 64;
   constexpr int TM = WM / MM::BLK, TN = WN / MM::BLK;
   // LDS row pitches, as in TileLoader
@@ -188,7 +181,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParamsT<T>& p, int bx, int b
   }
   const bool do_bias = (EPI == EPI_DW_SGD || EPI == EPI_DW_PARTIAL) && by == 0;
 
-  typename MM::acc_t acc[TM][TN];
+  MM::acc_t acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
