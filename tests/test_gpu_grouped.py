@@ -18,7 +18,7 @@ CASES = [
     ((37, 130, 40, 35, 33, 9, 10, 3), ("tanh",), 5, ("wide_dw_sgd",)),   # seven layers: two launches
     ((300, 400, 700, 260, 5), ("tanh",), 33, ("wide_bwd_piece", "bwd_fold")),
     ((64, 513, 1031, 7), ("sigmoid",), 17, ("wide_bwd_piece", "bwd_fold")),
-    ((20, 3000, 2900, 12), ("tanh", "tanh", "sigmoid"), 600, ("wide_dw",)),
+    ((20, 3000, 2900, 12), ("tanh", "tanh", "sigmoid"), 600, ("wide_dw_sgd", "wide_dw_partial")),   # one piece and several
 ]
 
 
@@ -51,7 +51,8 @@ def test_grouped_steps_f64(dims, acts, batch, kernels):
         nf.nf_net_destroy(net)
     ref, G = mlp.train_batch(theta.astype(np.float64), dims, parity.full_acts(dims, acts),
                              X, Y, 0.2, 1, precision="f64")
-    # sums of at most 1100 products, each side within 1100 2^-53 of exact
+    # sums of at most 1100 products, each side within 1100 2^-53 of exact, through every layer
+    bound = 2 * len(dims) * 1100 * 2.0 ** -53
     for got, want in ((p, ref), (g, G)):
         rms = np.sqrt(np.mean(np.asarray(want) ** 2))
-        assert np.max(np.abs(got - want) / np.maximum(np.abs(want), rms)) < 1e-9
+        assert np.max(np.abs(got - want) / np.maximum(np.abs(want), rms)) < bound

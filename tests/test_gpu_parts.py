@@ -1,6 +1,7 @@
 """The range of the fp32 products that are formed from three bf16 parts per
 operand: small operands beside large partners, subnormal operands and long sums of
-them give what fp32 arithmetic gives, in every kernel that splits its operands.
+them, and operands too large for the parts (whose sums are formed again), give what
+fp32 arithmetic gives, in every kernel that splits its operands.
 
 Bound: an fp32 sum of k products of the absolute values, and a rounding to the
 smallest subnormal number.  The large partners keep every sum far from underflow."""
@@ -44,14 +45,16 @@ def _check(torch, got, a, b):
     assert off <= 0, (off, ((got.double() - ref).norm() / ref.norm()).item())
 
 
-# rows of the small operand, as powers of ten: below 2^-108 the third part was lost, below
-# 2^-117 the second, below 2^-126 all; the last are a few times 2^-149
-SMALL = [-33, -34, -35, -36, -37, -38, -39, -41, -44]
+# Powers of ten of an operand's rows, and the other operand's.  Small: below 2^-108 the third
+# unscaled part is lost, below 2^-117 the second, below 2^-126 all; the last are a few times
+# 2^-149.  Large: from 2^105 on a scaled part is infinite; the rows beside are not.
+RANGES = {"small": ([-33, -34, -35, -36, -37, -38, -39, -41, -44], 1e30),
+          "large": ([0, 31, 32, 0, 35, 37, 38], 1e-30)}
 
 
-def _small_rows(torch, x):
-    scale = torch.tensor([10.0 ** e for e in SMALL], dtype=torch.float64, device="cuda")
-    reps = (x.shape[0] + len(SMALL) - 1) // len(SMALL)
+def _rows(torch, x, powers):
+    scale = torch.tensor([10.0 ** e for e in powers], dtype=torch.float64, device="cuda")
+    reps = (x.shape[0] + len(powers) - 1) // len(powers)
     return (x.double() * scale.repeat(reps)[:x.shape[0], None]).float()
 
 
@@ -66,19 +69,21 @@ FORWARD = [
 
 @pytest.mark.parametrize("shape,kernel", FORWARD)
 @pytest.mark.parametrize("side", ["samples", "weights"])
-def test_forward(shape, kernel, side):
+@pytest.mark.parametrize("size", RANGES)
+def test_forward(shape, kernel, side, size):
     torch = torch_cuda()
     m, k, n = shape
+    powers, partner = RANGES[size]
     rand = _rand(torch, m + k)
     x, w = rand(m, k), rand(n, k)
     if side == "samples":
-        x, w = _small_rows(torch, x), 1e30 * w
+        x, w = _rows(torch, x, powers), partner * w
     else:
-        x, w = 1e30 * x, _small_rows(torch, w)
+        x, w = partner * x, _rows(torch, w, powers)
     out = torch.empty(m, n, device="cuda")
     nf, h = _net((k, n), ("relu",), (w, np.zeros(n)))
     try:
-        note(f"small operands forward {shape} {side}")
+        note(f"{size} operands forward {shape} {side}")
         assert kernel in _names(nf, h, lambda: nf.nf_forward(h, x, out))
     finally:
         nf.nf_net_destroy(h)
@@ -87,15 +92,17 @@ def test_forward(shape, kernel, side):
 
 @pytest.mark.parametrize("m,k,n", [(33, 40, 17), (40, 785, 100), (3000, 129, 128), (10000, 784, 100)])
 @pytest.mark.parametrize("side", ["samples", "weights"])
-def test_forward_skinny(m, k, n, side):
+@pytest.mark.parametrize("size", RANGES)
+def test_forward_skinny(m, k, n, side, size):
     """Through a second layer that passes the first one's values on."""
     torch = torch_cuda()
+    powers, partner = RANGES[size]
     rand = _rand(torch, m + k)
     x, w = rand(m, k), rand(n, k)
     if side == "samples":
-        x, w = _small_rows(torch, x), 1e30 * w
+        x, w = _rows(torch, x, powers), partner * w
     else:
-        x, w = 1e30 * x, _small_rows(torch, w)
+        x, w = partner * x, _rows(torch, w, powers)
     out = torch.empty(m, n, device="cuda")
     # (several units, so that the net is not a narrow one)
     wide = max(n, 40)
@@ -105,7 +112,7 @@ def test_forward_skinny(m, k, n, side):
     w2[torch.arange(n), torch.arange(n)] = 1
     nf, h = _net((k, wide, n), ("relu",), (w1, np.zeros(wide), w2, np.zeros(n)))
     try:
-        note(f"small operands skinny {m} {k} {n} {side}")
+        note(f"{size} operands skinny {m} {k} {n} {side}")
         assert "fwd_skinny" in _names(nf, h, lambda: nf.nf_forward(h, x, out))
     finally:
         nf.nf_net_destroy(h)
@@ -122,17 +129,19 @@ TENDENCIES = [
 
 
 @pytest.mark.parametrize("shape,kernel", TENDENCIES)
-def test_tendencies(shape, kernel):
+@pytest.mark.parametrize("size", RANGES)
+def test_tendencies(shape, kernel, size):
     """One relu layer without weights: its deltas are its biases minus the targets."""
     torch = torch_cuda()
     b, k, n = shape
+    powers, partner = RANGES[size]
     rand = _rand(torch, b + k)
     bias = torch.full((n,), 1e-44, device="cuda")
-    y = -_small_rows(torch, rand(n, b)).t().contiguous()
-    x = 1e30 * rand(b, k)
+    y = -_rows(torch, rand(n, b), powers).t().contiguous()
+    x = partner * rand(b, k)
     nf, h = _net((k, n), ("relu",), (np.zeros(n * k), bias))
     try:
-        note(f"small operands tendencies {shape}")
+        note(f"{size} operands tendencies {shape}")
         assert kernel in _names(nf, h, lambda: nf.nf_train_batch(h, x, y, 0.0, 1))
         got = torch.from_numpy(nf.nf_get_grads(h)[:n * k]).cuda().view(n, k)
     finally:
@@ -150,20 +159,22 @@ DELTAS = [
 
 
 @pytest.mark.parametrize("shape,kernel", DELTAS)
-def test_deltas(shape, kernel):
+@pytest.mark.parametrize("size", RANGES)
+def test_deltas(shape, kernel, size):
     """A tanh layer at zero, whose f' is 1, below a relu layer whose deltas are
     its biases minus the targets; unit samples make the first layer's
     tendencies its deltas."""
     torch = torch_cuda()
     b, n1, n2 = shape
+    powers, partner = RANGES[size]
     rand = _rand(torch, b + n1)
     bias = torch.full((n2,), 1e-44, device="cuda")
-    y = -_small_rows(torch, rand(b, n2))
-    w2 = 1e30 * rand(n2, n1)
+    y = -_rows(torch, rand(b, n2), powers)
+    w2 = partner * rand(n2, n1)
     x = torch.eye(b, device="cuda")
     nf, h = _net((b, n1, n2), ("tanh", "relu"), (np.zeros(n1 * b), np.zeros(n1), w2, bias))
     try:
-        note(f"small operands deltas {shape}")
+        note(f"{size} operands deltas {shape}")
         assert kernel in _names(nf, h, lambda: nf.nf_train_batch(h, x, y, 0.0, 1))
         got = torch.from_numpy(nf.nf_get_grads(h)[:n1 * b]).cuda().view(n1, b)
     finally:

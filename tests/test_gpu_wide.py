@@ -50,16 +50,18 @@ def _single_layer(rng, m, k, n):
     return np.concatenate([w.ravel(), b]), w, b
 
 
-# one tile of each size, and a matrix with a tile that stays ordinary beside
-# the one that is done again
-SHAPES = [(70, 203, 150), (300, 96, 2500), (4352, 64, 4352)]
+# each tile of the forward kernels, by the name that must appear: the ones that are
+# done again lie among ones that stay ordinary
+SHAPES = [(70, 203, 150, "64x64"), (300, 96, 2500, "64x64"), (4352, 64, 4352, "128x128"),
+          (4096, 1024, 4096, "256x256")]
 
 
-@pytest.mark.parametrize("m,k,n", SHAPES)
-def test_operands_past_bf16(m, k, n):
-    """Infinities, NaN, values that round to infinity in bf16 and values whose
-    parts are subnormal give what fp32 arithmetic gives: relu of the fp64 sums,
-    to the bound of an fp32 sum of k products, and the same infinities and NaN."""
+@pytest.mark.parametrize("m,k,n,tile", SHAPES)
+def test_operands_past_bf16(m, k, n, tile):
+    """Infinities, NaN, values that round to infinity in bf16 and a row of values
+    near 1e-36 give what fp32 arithmetic gives: relu of the fp64 sums, to the
+    bound of an fp32 sum of k products, and the same infinities and NaN.  (The
+    full range of small operands is in test_gpu_parts.py.)"""
     rng = np.random.default_rng(m + k + n)
     theta, w, b = _single_layer(rng, m, k, n)
     X = rng.uniform(-1, 1, (m, k)).astype(np.float32)
@@ -69,11 +71,15 @@ def test_operands_past_bf16(m, k, n):
     X[3, 7] = np.nan
     X[4, :] = 0
     X[4, 8] = big                      # finite, but bf16(x) is infinite
-    X[5, :] *= np.float32(1e-36)       # parts below the smallest normal number
+    X[5, :] *= np.float32(1e-36)
     X[6, 9], X[6, 10] = np.inf, -np.inf
     note(f"operands past bf16 m={m} k={k} n={n}")
     with GpuNet((k, n), ("relu",), theta) as net:
+        net.nf.nf_profile(net.h, 1)
         out = net.forward(to_dev(X)).astype(np.float64)
+        names = {q["name"] for q in net.nf.nf_profile_read(net.h)}
+        net.nf.nf_profile(net.h, 0)
+        assert f"wide_fwd_out_{tile}" in names, names
         # without the biases the tiny row is not absorbed
         theta0 = np.concatenate([w.ravel(), np.zeros(n, np.float32)])
         net.nf.nf_set_params(net.h, theta0)
