@@ -168,7 +168,8 @@ struct SkinnyGroup {
   int n;
 };
 hipError_t launch_dw_skinny_group(SkinnyGroup g, hipStream_t s);
-// The same for fp64 layers (input tiles of 32, 16-byte loads of two doubles).
+// The same for fp64 layers (input tiles of 32, 16-byte loads of two doubles, so
+// both operands need 16-byte aligned rows with pitches of whole vectors).
 struct SkinnyGroup64 {
   GemmParamsT<double> p[GEMM_GROUP_MAX];
   int start[GEMM_GROUP_MAX + 1];

@@ -6,25 +6,35 @@
 // (nf_parts.h).
 //
 // Why: the fp32 matrix instruction gives 64 flops a clock and SIMD, the bf16
-// one 1024, so six of them are worth 171, 2.7 times as many.  The sums are
-// no less exact: 6 roundings of the accumulator for 16 k, not 8.  Relative
-// errors against fp64, one 32 x 32 block over k uniform operands, six bf16
-// products against v_mfma_f32_32x32x2_f32: k = 16 3.4e-8 / 7.4e-8, 784 4.5e-7 /
-// 5.0e-7, 4096 9.7e-7 / 1.1e-6 (operands of both signs); 5.3e-7 / 8.4e-7
-// (positive operands, k = 4096).
+// one 1024, so six of them are worth 171, 2.7 times as many.  The sums are no
+// less exact: in the 64 x 64 and 128 x 128 tiles the leading products have
+// accumulators of their own, rounded once for 16 k, in the 256 x 256 tile all
+// six share one, 6 roundings for 16 k, not 8.  Relative errors (2-norm)
+// against fp64, operands of both signs / positive, x 1e-7, and those of the
+// fp32 instruction in the contraction that this replaced:
+//   tile        contraction                            parts        fp32
+//   64 x 64     600 x 300, k = 1024 in 8 pieces        0.8 / 0.4    2.1 / 0.7
+//   128 x 128   4096 x 1024, k = 784                   1.6 / 1.4    5.0 / 3.9
+//               tendencies 1024 x 1024, k = 4096       1.9 / 0.9    5.8 / 2.4
+//   256 x 256   8192 x 4096, k = 256                   2.4 / 1.8    2.9 / 2.2
+//               k = 1024                               4.9 / 2.9    5.7 / 4.3
+//               k = 4096                               10.0 / 5.3   11.5 / 8.4
+//               tendencies 4096 x 4096, k = 8192       14.4 / 8.5   16.2 / 13.4
 //
-// What bounds it: on large problems the power limit (8192 x 4096 x 4096 runs
-// at 1.7 - 1.9 GHz with the matrix cores 70% busy), else the vector
-// instructions of the split, 13 for two values, which a wave does not overlap
-// with its own matrix instructions (a second wave on the SIMD does: per
-// matrix instruction 39 clocks alone, 64 with four vector instructions in the
-// same wave, 43 with them in another).  Hence tiles as large as the grid
-// allows, each operand split once per tile on its way to LDS, and for the
-// 64 x 64 tile loading waves of their own.
-// Measured (random operands, sustained, against the fp32 matrix kernel this
-// replaces): forward 8192 x 4096 x 4096 1116 us, 246 TFLOP/s, against 1968;
-// forward 4096 x 1024 x 1024 48.5 us against 77; tendencies 1024 x 1024 over
-// 4096 in four pieces 48 us against 74; 3003 x 517 x 1001 32 us against 34.
+// What bounds it: on large problems the power limit and the matrix cores (the
+// clock and how busy they are: profiles/gemm_kernels__4096x4-10_batch8192.md),
+// else the vector instructions of the split, 13 for two values, which a wave
+// does not overlap with its own matrix instructions (a second wave on the SIMD
+// does: per matrix instruction 39 clocks alone, 64 with four vector
+// instructions in the same wave, 43 with them in another).  Hence tiles as
+// large as the grid allows, each operand split once per tile on its way to
+// LDS, and for the 64 x 64 tile loading waves of their own.
+// Measured (us, random operands, sustained, against the fp32 contraction that
+// this replaced, on one card): forward 8192 x 4096 x 4096 1166, 236 TFLOP/s,
+// against 1931; 4096 x 1024 x 1024 58 against 85; 10000 x 1024 x 1024 157 against 224;
+// tendencies 1024 x 1024 over 4096 in four pieces 58 against 86, 4096 x 4096 over
+// 8192 1117 against 2045; 3003 x 517 x 1001 34 against 47 and a fold; 16 x 255 x 300 7.4
+// against 9.3.
 #pragma once
 
 #include <type_traits>
@@ -47,7 +57,7 @@ constexpr int wide_lds(int BM, int BN, int BK, int nb) {
 
 // Global -> registers -> LDS of one R x BK operand tile X(r, k) by NT threads,
 // Q quads of 4 values each.  In LDS each of the three parts is [BK / 8][R][8]
-// bf16 (the groups of 8 k 128 bytes apart, in other banks): the 8
+// bf16 (the groups of 8 k 64 or 128 bytes further apart, in other banks): the 8
 // consecutive k of a row that a lane's operand takes are one 16-byte chunk,
 // and the 32 rows of a half-wave's read are contiguous.
 // KC: quad i holds 4 consecutive k of one row, loaded at once (the hardware
