@@ -978,7 +978,10 @@ hipError_t launch_narrow_pack_w1(const float* W1, int64_t ldw, int d1, int d0, f
 // The per-sample kernel for this pass: inference over batches above
 // NARROW_SMALL_BATCH takes the persistent kernel when W_1 fits its matrix
 // waves' registers (d0 <= 8 waves x NI_MC_MAX chunks x 16 = 1024) and every
-// workgroup's input rows fit below NI_OOB bytes.
+// workgroup's input rows fit below NI_OOB bytes.  Odd rows take the 16-sample
+// kernel there, since the persistent one loads whole vectors or none and has no
+// form for a row's partial last one (10000 samples: 785-30-10 16.9 us, 784-30-10
+// on the persistent kernel 14.2).
 constexpr int NI_MC_MAX = 8;
 
 int narrow_infer_grid(const NarrowFwdParams& p) {
