@@ -207,12 +207,22 @@ int64_t ws_layout(const nf_net* n, int64_t batch, std::vector<int64_t>* aoff,
     if (l < L) {
       (*aoff)[l] = total;
       total += sz;
-      (*foff)[l] = total;
-      total += sz;
     }
     (*doff)[l] = total;
     total += sz;
   }
+  // last, so that pieces may begin where the medium path leaves them unused
+  for (int l = 1; l < L; ++l) {
+    (*foff)[l] = total;
+    total += round_up(batch * n->layers[l].lda, kAlign);
+  }
+  return total;
+}
+
+// elements of the f'(z) buffers
+int64_t ws_fprime(const nf_net* n, int64_t batch) {
+  int64_t total = 0;
+  for (int l = 1; l < num_layers(n); ++l) total += round_up(batch * n->layers[l].lda, kAlign);
   return total;
 }
 
@@ -434,6 +444,30 @@ nf_status launch(nf_net* n, int epi, bool akc, bool bkc, bool av, bool bv, int n
   }
 }
 
+// elements that a step of `batch` samples has for its pieces in the array of
+// nf_train_batch_noalloc, on the medium path with the f'(z) buffers, which it
+// has no use for (negative: its per-sample buffers don't fit)
+int64_t noalloc_room(const nf_net* n, int64_t batch, bool medium) {
+  const int L = num_layers(n);
+  const int64_t f = ws_fprime(n, batch);
+  int64_t ws = f;
+  for (int l = 1; l <= L; ++l)
+    ws += (l < L ? 2 : 1) * round_up(batch * n->layers[l].lda, kAlign);
+  const int64_t room = (int64_t)(NF_NOALLOC_SCRATCH_BYTES / n->esz) - ws;
+  return room >= 0 && medium ? room + f : room;
+}
+
+// The most pieces of a forward contraction's M x N sums: `most`, or as many of
+// them as leave the step within that array where at least `least` do.  Other
+// entries allocate their pieces but take the same cut, since they promise the same
+// bits (1123-21-25-12-30-49-45-36-2 at 17238 samples would need 51.6 MB of 50.3).
+int64_t piece_cap(const nf_net* n, int64_t M, int64_t N, int64_t most, int64_t least, bool medium) {
+  if (n->dtype != nf::DT_F32 || most <= 1) return most;
+  const int64_t pstride = round_up(M * round_up(N, 4), kAlign), room = noalloc_room(n, M, medium);
+  if (room < least * pstride) return most;
+  return std::min(most, std::max<int64_t>(1, room / pstride));
+}
+
 // The cut of a forward contraction (M samples, N units, K inputs) over its
 // k range.  At most the pieces that bring the 64 x 64 tile grid to twice the
 // CU count, of at least 128 inputs each, 16 at most; none where K < 256 or
@@ -451,7 +485,9 @@ nf::KSplit fwd_split(const nf_net* n, int64_t M, int64_t N, int64_t K, bool smal
   const int64_t want = 2 * (int64_t)device_cus(n);
   if ((small_tile_only && pick_tile(M, N, 1) != nf::TILE_64x64) || tiles >= want || K < 256)
     return nf::KSplit{1, (int)K};
-  const int64_t most = std::min<int64_t>({(want + tiles - 1) / tiles, K / 128, 16});
+  // a general net in one piece needs no room for it
+  const int64_t most = piece_cap(n, M, N, std::min<int64_t>({(want + tiles - 1) / tiles, K / 128, 16}),
+                                 small_tile_only ? 0 : 1, !small_tile_only);
   if (n->dtype == nf::DT_F64) return nf::k_split(K, most);
   nf::KSplit best{1, (int)K};
   double cost = 0.0;
@@ -490,11 +526,13 @@ SkinnyFwdPlan fwd_skinny_plan(const nf_net* n, int64_t M, int64_t N, int64_t K) 
   const int64_t blocks = (N + 15) / 16;
   nf::KSplit cuts[16];
   int count = 0, most = -1;
-  int64_t least = -1;
+  int64_t least = -1, cap = 16;
   for (int want = 1; want <= 16; ++want) {
     const nf::KSplit ks = nf::k_split(K, want);
     const int64_t quads = 4 * ((ks.sub_len + 15) / 16);
     if (16 * blocks * (quads % 2 == 1 ? quads : quads + 1) * 16 + 16 > 160 * 1024) continue;
+    if (count == 0) cap = piece_cap(n, M, N, cap, ks.nsplit, true);
+    else if (ks.nsplit > cap) break;
     const int64_t per_cu = ((M + 127) / 128 * ks.nsplit + ncu - 1) / ncu;
     const int64_t steps = per_cu * ((ks.sub_len + 15) / 16);
     cuts[count] = ks;
@@ -983,10 +1021,21 @@ bool narrow_rows_ok(const nf_net* n, const T* x) {
 // medium path splits it (us a step, narrow and medium: 785-30-10 at 3000 samples 22.4
 // and 27.2, 5000 36.9 and 28.5; 5-26-16 22.0 and 21.2, 16000 84.9 and 29.9;
 // 1027-12-10 28.0 and 25.2).
+// They keep it where the pieces of the other path, which they have no need of, would
+// not fit in the array of nf_train_batch_noalloc though the per-sample buffers do.
 constexpr int64_t NARROW_ODD_BATCH = 3000;
 template <class T>
+int64_t pieces_need(const nf_net* n, int64_t batch, int shards);
+template <class T>
+bool medium_layout(const nf_net* n, int64_t batch, nf::MediumParamsT<T>* p);
+
+template <class T>
 bool narrow_step_ok(const nf_net* n, const T* x, int64_t batch, int shards) {
-  return shards == 1 && narrow_rows_ok<T>(n, x) && (vec_ok(x, n->dims[0]) || batch <= NARROW_ODD_BATCH);
+  if (shards != 1 || !narrow_rows_ok<T>(n, x)) return false;
+  if (vec_ok(x, n->dims[0]) || batch <= NARROW_ODD_BATCH) return true;
+  nf::MediumParamsT<T> mp{};
+  const int64_t room = noalloc_room(n, batch, medium_layout<T>(n, batch, &mp));
+  return room >= 0 && pieces_need<T>(n, batch, shards) > room;
 }
 
 template <class T>
@@ -1749,7 +1798,12 @@ nf_status train_batch(nf_net* net, const T* d_x, const T* d_y, int64_t batch, do
 // backward pass starts) or the tendency pieces, whichever is larger.
 template <class T>
 int64_t partial_need(const nf_net* n, const T* x, int64_t batch, int shards) {
-  if (narrow_step_ok<T>(n, x, batch, shards)) return 0;
+  return narrow_step_ok<T>(n, x, batch, shards) ? 0 : pieces_need<T>(n, batch, shards);
+}
+
+// the same off the narrow kernels
+template <class T>
+int64_t pieces_need(const nf_net* n, int64_t batch, int shards) {
   std::vector<DwPiece> pieces;
   int64_t need = dw_plan(n, batch, shards, &pieces);
   nf::MediumParamsT<T> mp{};
@@ -1829,7 +1883,11 @@ nf_status train_batch_noalloc(nf_net* net, const float* d_x, const float* d_y, i
     std::vector<int64_t> aoff, foff, doff;
     const int64_t ws = round_up(ws_layout(net, batch, &aoff, &foff, &doff), kAlign);
     const int64_t part = partial_need<float>(net, d_x, batch, n_shards);
-    const double need = (double)(ws + part) * (double)net->esz;
+    // the medium path's pieces begin in the f'(z) buffers
+    nf::MediumParamsT<float> mp{};
+    const bool medium = part > 0 && medium_layout<float>(net, batch, &mp);
+    const int64_t poff = ws - (medium ? ws_fprime(net, batch) : 0);
+    const double need = (double)std::max(ws, poff + part) * (double)net->esz;
     if (need > (double)NF_NOALLOC_SCRATCH_BYTES)
       return fail(NF_ESHAPE, "this step needs " + std::to_string((int64_t)need) +
                                  " bytes of scratch; nf_train_batch_noalloc has " +
@@ -1852,7 +1910,7 @@ nf_status train_batch_noalloc(nf_net* net, const float* d_x, const float* d_y, i
     const int prof = net->prof;
     ws_assign(net, sbase, aoff, foff, doff);
     net->ws_batch = batch;
-    net->partial = sbase + ws * (int64_t)net->esz;
+    net->partial = sbase + poff * (int64_t)net->esz;
     net->partial_elems = part;
     net->borrowed = true;
     net->prof = 0;

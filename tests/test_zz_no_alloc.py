@@ -72,6 +72,46 @@ def test_noalloc_step_equals_train_batch(dims, acts, batches, shards, eta):
         nf.nf_net_destroy(b)
 
 
+# Steps that fill the array: odd input rows of narrow nets, whose pieces lie where f'(z)
+# has its place (with one layer, no f'(z): the narrow kernels), and nets whose first
+# layer would be cut into more pieces than the array holds.
+NEAR = [
+    # dims, batch, shards
+    ((5, 26, 16), 90000, 1),
+    ((785, 30, 10), 96000, 1),
+    ((7, 20, 11, 9), 55000, 1),
+    ((785, 10), 300000, 1),
+    ((618, 79, 25), 25243, 1),
+    ((608, 107, 7), 18078, 2),
+    ((1123, 21, 25, 12, 30, 49, 45, 36, 2), 17238, 2),
+]
+
+
+@pytest.mark.parametrize("dims,batch,shards", NEAR)
+def test_noalloc_near_the_limit(dims, batch, shards):
+    """Taken, and the same bits as nf_train_batch."""
+    import torch
+    from paper_1902_06714_amd import nf
+    note(f"noalloc near the limit dims={dims} batch={batch} shards={shards}")
+    theta, _, _ = _problem(dims, sum(dims), 1)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(batch)
+    x = torch.rand(batch, dims[0], generator=g, device="cuda")
+    y = torch.rand(batch, dims[-1], generator=g, device="cuda")
+    a = nf.nf_net_create(dims, ["tanh"])
+    b = nf.nf_net_create(dims, ["tanh"])
+    try:
+        for h in (a, b):
+            nf.nf_set_params(h, theta)
+        nf.nf_train_batch(a, x, y, 0.5, shards)
+        nf.nf_train_batch_noalloc(b, x, y, 0.5, shards)
+        assert np.array_equal(nf.nf_get_params(a), nf.nf_get_params(b))
+        assert np.array_equal(nf.nf_get_grads(a), nf.nf_get_grads(b))
+    finally:
+        nf.nf_net_destroy(a)
+        nf.nf_net_destroy(b)
+
+
 def test_noalloc_refuses_steps_beyond_the_scratch():
     """784-1024^3-10 at 4096 samples needs about 150 MB of per-sample buffers:
     refused with NF_ESHAPE, nothing run, the net unchanged."""
