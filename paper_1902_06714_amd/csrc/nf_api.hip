@@ -515,12 +515,13 @@ nf::KSplit fwd_split(const nf_net* n, int64_t M, int64_t N, int64_t K, bool smal
 // Among the piece counts whose W is at most 160 KB in fp32 (two slices of its
 // parts in LDS) and up to the one with the fewest k-groups on the busiest CU
 // at 128 samples, the least time of the two launches: a k-group of 32 inputs
-// costs the forward kernel about 0.3 us and 0.04 per block of 16 units for its
-// W and, at 128 samples, 0.1 per block for its products; a piece past the second
-// costs the per-sample kernel about 0.45 us (it loads two ahead).  Over 400 shapes of
-// 33 to 4001 inputs, 40 to 128 units and 1 to 10000 samples the choice takes 1.4% more
-// than the best one on the mean (1539 inputs, 100 units, 45 samples: inference 15.6 us,
-// 18.9 in the 5 pieces that 0.15 us a k-group and 0.6 a piece gave).
+// costs the forward kernel about 0.2 us and 0.03 per block of 16 units for its
+// W and, at 128 samples, 0.12 per block for its products; a piece past the second
+// costs the per-sample kernel about 0.3 us (it loads two ahead), or all of them their
+// way through memory, at about 5 TB/s, where that takes longer (618-128-10 at 50000
+// samples, a step in two pieces 201 us, in five 225; fewer than 64 units no faster).
+// Over 1293 shapes of 33 to 4001 inputs, 4 to 128 units and 1 to 100000 samples the
+// choice takes 0.6% more than the best one on the mean, 15% at worst.
 SkinnyFwdPlan fwd_skinny_plan(const nf_net* n, int64_t M, int64_t N, int64_t K) {
   const int64_t ncu = device_cus(n);
   const int64_t blocks = (N + 15) / 16;
@@ -548,10 +549,11 @@ SkinnyFwdPlan fwd_skinny_plan(const nf_net* n, int64_t M, int64_t N, int64_t K) 
     for (int rows : {128, 32}) {
       const nf::KSplit& ks = cuts[i];
       const int64_t per_cu = ((M + rows - 1) / rows * ks.nsplit + ncu - 1) / ncu;
-      const double group = 0.3 + 0.0375 * (double)blocks +
-                           0.1 * (double)(rows == 128 ? blocks : (blocks + 3) / 4);
+      const double group = 0.2 + 0.03 * (double)blocks +
+                           0.12 * (double)(rows == 128 ? blocks : (blocks + 3) / 4);
       const double c = (double)per_cu * (1.0 + group * (double)((ks.sub_len + 31) / 32)) +
-                       0.45 * (double)std::max(0, ks.nsplit - 2);
+                       std::max(0.3 * (double)std::max(0, ks.nsplit - 2),
+                                2.0 * 4.0 * (double)M * (double)std::max<int64_t>(N, 64) * ks.nsplit / 5e6);
       if (best.ks.nsplit == 0 || c < cost) {
         best.ks = ks;
         best.rows = rows;
