@@ -901,10 +901,14 @@ nf_status run_backward_update(nf_net* n, const T* x, int64_t batch, double eta, 
         const Piece& pj = pieces[j];
         const nf::GemmParamsT<T> p = piece_params(pj);
         // The fp32 kernel reads input rows of any pitch, but those that are not
-        // whole vectors no faster than the wide kernels where there is much of
-        // them (us a step, skinny and wide: 1958-121-80-3 at 7970 samples 148 and 121,
-        // at 2049 57 and 63; 785-120-10 at 10000 68.4 and 68.2; 1957-60-10 70 and 79)
-        if (sizeof(T) == 4 && p.M > 96 && !vec_ok(p.B, p.ldb) &&
+        // whole vectors no faster than the wide kernels where there is much of them
+        // and the layer's workgroups are clearly more than one for each CU (us a step,
+        // skinny and wide, at 121 units, and the workgroups per CU: 1957 inputs, 7970
+        // samples in 5 shards 121 and 106, 1.21; 14000 in one 168 and 180, 0.97; 701 inputs,
+        // 28361 samples 153 and 142, 1.38; 503 inputs 113 and 119, 1.0; 1001 inputs 181
+        // and 191, 1.0, and 2048 samples 41 and 43)
+        const double wgs = (double)((p.N + nf::SKINNY_TILE_F32 - 1) / nf::SKINNY_TILE_F32) * shards * pj.nsub;
+        if (sizeof(T) == 4 && p.M > 96 && !vec_ok(p.B, p.ldb) && wgs > 1.1 * device_cus(n) &&
             (double)p.M * (double)p.N * (double)batch > 1e9)
           continue;
         if (p.M > nf::SKINNY_MAX_UNITS || !vec_ok(p.A, p.lda) ||
