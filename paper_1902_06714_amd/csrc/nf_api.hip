@@ -1330,15 +1330,18 @@ nf_status train_step(nf_net* n, const T* x, const T* y, int64_t batch, double et
 }
 
 // Medium nets whose inference is faster layer by layer: fp32 nets of two layers, where
-// that saves no launch, on many samples of few inputs (us, medium path and layers: 64-
-// 103-38 at 8192 samples 16.3 and 13.4, 14616 23.7 and 16.5, but 4096 11.8 and 13.3; 784-
-// 100-10 at 10000 27.4 and 32.5; 64-100-100-10 at 10000 21.6 and 24.9) and on the fewest
-// samples of many inputs (1824-120-6, one sample 14.9 and 13.9, 2048 samples
-// 25.6 and 23.3, 3000 26.4 and 28.7; 784-100-10, one sample 13.1 and 13.6).
+// that saves no launch, on many samples of few inputs and many units (layers against
+// medium path at 12000 to 100000 samples: over 96 units and up to 256 inputs 0.87 on the
+// mean, 1.08 at worst, 119-103-10 at 30000 samples 23.5 and 28.1 us; of 66 to 90 units
+// 0.90 and 1.05 up to 31 inputs, but 1.04 and 1.23 from 64 inputs on; at 8192 samples
+// 64-103-10 13.0 and 12.0) and on few samples of many inputs and units (2500-100-10, one
+// sample 12.9 and 15.2, 256 samples 15.7 and 17.8; 1824-120-6, 256 samples 15.9 and 16.9;
+// 1024-100-10 14.6 and 14.3; 1300-64-10, one sample 12.0 and 11.2).
 template <class T>
 bool infer_by_layer(const nf_net* n, int64_t batch) {
   return sizeof(T) == 4 && num_layers(n) == 2 &&
-         ((n->dims[0] <= 256 && n->dims[1] > 64 && batch >= 8192) || (n->dims[0] >= 1024 && batch <= 16));
+         ((batch >= 12000 && n->dims[1] > 64 && n->dims[0] <= (n->dims[1] > 96 ? 256 : 32)) ||
+          (batch <= 256 && n->dims[1] > 96 && n->dims[0] >= 1500));
 }
 
 // f(z_L) of `batch` samples into out [batch][d_L] (inference, no stash)

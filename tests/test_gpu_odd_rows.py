@@ -36,10 +36,14 @@ CASES = [
     ((1961, 97, 5), ("tanh", "sigmoid"), 5265, 5, ("fwd_skinny", "wide_dw_partial_128x128", "dw_skinny"),
      "medium_infer"),
     # inference layer by layer
-    ((255, 65, 3), ("tanh", "sigmoid"), 8192, 1, ("fwd_skinny",), "wide_fwd_out_64x64"),
-    ((255, 64, 3), ("tanh", "sigmoid"), 8192, 1, ("fwd_skinny",), "medium_infer"),
-    ((1025, 40, 3), ("tanh", "sigmoid"), 16, 1, ("fwd_skinny",), "wide_fwd_out_64x64"),
-    ((1025, 40, 3), ("tanh", "sigmoid"), 17, 1, ("fwd_skinny",), "medium_infer"),
+    ((255, 97, 3), ("tanh", "sigmoid"), 12000, 1, ("fwd_skinny",), "wide_fwd_out_64x64"),
+    ((255, 97, 3), ("tanh", "sigmoid"), 11999, 1, ("fwd_skinny",), "medium_infer"),
+    ((255, 96, 3), ("tanh", "sigmoid"), 12000, 1, ("fwd_skinny",), "medium_infer"),
+    ((31, 65, 3), ("tanh", "sigmoid"), 12000, 1, ("fwd_skinny",), "wide_fwd_out_64x64"),
+    ((33, 65, 3), ("tanh", "sigmoid"), 12000, 1, ("fwd_skinny",), "medium_infer"),
+    ((1501, 97, 3), ("tanh", "sigmoid"), 256, 1, ("fwd_skinny",), "wide_fwd_out_64x64"),
+    ((1501, 97, 3), ("tanh", "sigmoid"), 257, 1, ("fwd_skinny",), "medium_infer"),
+    ((1501, 96, 3), ("tanh", "sigmoid"), 256, 1, ("fwd_skinny",), "medium_infer"),
 ]
 
 
